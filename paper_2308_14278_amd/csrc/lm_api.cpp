@@ -207,7 +207,7 @@ struct lm_map {
     int64_t ncx = 0, ncy = 0, n1x = 0, n1y = 0;
     int nl1x = 0, nl1y = 0;
     // device buffers
-    DevBuf lx, ly, lmd, lxf, lyf, lmf, lI, lJ, cell_start, coef, counts_own, n_out, ptab, l1exp;
+    DevBuf lx, ly, lmd, lxf, lyf, lmf, lI, lJ, cell_start, coef, counts_own, n_out, l1exp;
     std::vector<int32_t> h_start;  // host copy of the level-1 CSR
     uint64_t* counts = nullptr;  // own or bound
     bool bound = false;
@@ -399,7 +399,6 @@ LmDesc make_desc(const lm_map* m, int64_t i0, int64_t j0, int64_t i1, int64_t j1
     d.lJ = m->lJ.as<int32_t>();
     d.cell_start = m->cell_start.as<int32_t>();
     d.coef = m->coef.as<LmCoef>();
-    d.ptab = m->ptab.as<float>();
     d.Q = g.scheme == LM_SCHEME_INTERP ? g.far_order : 0;
     d.n1x = m->n1x;
     {
@@ -772,12 +771,6 @@ lm_status lm_create(const lm_geometry* g, lm_map** out)
     m->counts = m->counts_own.as<uint64_t>();
     LAUNCH_TRY(lm_launch_fill_u64((unsigned long long*)m->counts, (int64_t)npix, 0ull, nullptr));
     LAUNCH_TRY(lm_launch_fill_u64(m->n_out.as<unsigned long long>(), 1, 0ull, nullptr));
-    // column offsets of a level-2 cell and their powers, read by the shooting kernels
-    const int nptab = g->coarse + LM_PTAB_PAD;
-    if (m->ptab.ensure((size_t)LM_PTAB_ROWS * nptab * sizeof(float)) != hipSuccess)
-        return fail(LM_ENOMEM, "cannot allocate the column-offset table");
-    LAUNCH_TRY(lm_launch_ptab(make_desc(m.get(), 0, 0, 0, 0, Exec{}), m->ptab.as<float>(), nptab,
-                              nullptr));
     HIP_TRY(hipStreamSynchronize(nullptr));
     // empty lens set
     st = lm_set_lenses(m.get(), nullptr, nullptr, nullptr, 0);

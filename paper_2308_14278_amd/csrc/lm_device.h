@@ -55,15 +55,12 @@ struct UseTab {
 };
 
 // Waves per SIMD the shooting kernels must keep: the FP32 table paths are
-// issue-bound and needs 4 (at most 128 VGPRs with 256-thread workgroups, 4 per
-// CU).  The per-map kernel, whose descriptor arrives by value, would otherwise
-// allocate a few registers more than that and drop to 3; the hint holds it at
-// 128 (spilling per-unit values to scratch if it must).  The batch kernel
-// carries the same hint, with which the register allocator also schedules
-// the plain FP32 form a little tighter.
+// issue-bound and need 4 (at most 128 VGPRs with 256-thread workgroups, 4 per
+// CU); the FP64 sums fit 3 (168 VGPRs; at the 220 they took without the hint
+// two waves ran).
 template <int SCHEME, int PREC>
 struct MinWaves {
-    static constexpr int value = (SCHEME == 1 && PREC != 2) ? 4 : 1;
+    static constexpr int value = SCHEME != 1 ? 1 : PREC == 2 ? 3 : 4;
 };
 
 __device__ __forceinline__ void wave_sync_lds()
@@ -84,6 +81,21 @@ __device__ __forceinline__ unsigned wave_sum_u32(unsigned v)
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
+
+// The descriptors hold generic pointers, which a kernel that reads its
+// descriptor from memory (k_shoot_batch) could only follow with flat
+// instructions: those count against the LDS counter too, so every LDS wait
+// after a count added to the map would wait for that atomic's round trip.
+// global_ptr names the memory as global; const_ptr marks data no kernel of the
+// launch writes (lens index, coefficients), which wave-uniform addresses then
+// read through the scalar cache.
+template <class T>
+__device__ __forceinline__ T* global_ptr(T* p)
+{
+    return (T*)(__attribute__((address_space(1))) T*)p;
+}
+template <class T>
+using ConstP = const __attribute__((address_space(4))) T*;
 
 // Map constants the per-ray code reads, copied into registers once per unit so
 // that the global atomics of the counting step do not force reloads.
@@ -114,7 +126,7 @@ __device__ __forceinline__ Hot make_hot(const LmDesc& d)
     h.sny = d.sny;
     h.wx = d.wx;
     h.wy = d.wy;
-    h.counts = d.counts;
+    h.counts = global_ptr(d.counts);
     return h;
 }
 
@@ -147,9 +159,9 @@ __device__ __forceinline__ void cell_base(const LmDesc& d, int64_t ci, int64_t c
     double by = d.my * zy;
     if (d.fold) bx += (d.qx * zx + d.qy * zy) * zx;
     if (SCHEME == 1) {
-        const LmCoef& c = d.coef[cj * d.ncx + ci];
-        bx -= c.a0r;
-        by += c.a0i;
+        ConstP<LmCoef> c = (ConstP<LmCoef>)d.coef + (cj * d.ncx + ci);
+        bx -= c->a0r;
+        by += c->a0i;
     }
     ubx = (bx - d.bx0) * d.inv_sdx;
     uby = (by - d.by0) * d.inv_sdy;
@@ -461,8 +473,9 @@ __device__ __forceinline__ void near_row(const LmDesc& d, L1Cell c, int r, int& 
 {
     int row = c.J + r;  // padded row of J - H + r is (J - H + r) + H
     int base = row * d.nl1x + c.I;  // padded column of I - H is I
-    s = d.cell_start[base];
-    e = d.cell_start[base + 2 * d.H + 1];
+    ConstP<int32_t> cs = (ConstP<int32_t>)d.cell_start;
+    s = cs[base];
+    e = cs[base + 2 * d.H + 1];
 }
 
 template <int SCHEME>
@@ -471,6 +484,15 @@ __device__ __forceinline__ int list_count(const LmDesc& d, int64_t ci, int64_t c
     if (SCHEME == 0) return (int)d.nlens;
     const L1Cell c = l1_of(d, ci, cj);
     int n = 0;
+    if (d.H == 1) {  // the default 3x3 block: all six index loads in flight at once
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            int s, e;
+            near_row(d, c, r, s, e);
+            n += e - s;
+        }
+        return n;
+    }
     for (int r = 0; r <= 2 * d.H; ++r) {
         int s, e;
         near_row(d, c, r, s, e);
@@ -487,42 +509,54 @@ template <int PREC, bool PIX = PREC == 0 || PREC == kPrecCentred>
 __device__ __forceinline__ typename Prec<PREC>::L lens_value(const LmDesc& d, int idx, double zcx,
                                                             double zcy)
 {
+    const double *lx = global_ptr(d.lx), *ly = global_ptr(d.ly), *lmd = global_ptr(d.lmd);
+    const float *lxf = global_ptr(d.lxf), *lyf = global_ptr(d.lyf), *lmf = global_ptr(d.lmf);
     if constexpr (PREC == 2) {
-        return make_double4(d.lx[idx] - zcx, d.ly[idx] - zcy, d.lmd[idx], d.lmd[idx]);
+        return make_double4(lx[idx] - zcx, ly[idx] - zcy, lmd[idx], lmd[idx]);
     } else if constexpr (PREC == kPrecCentred) {
         // offset delta_k and c_k = m / delta_k (complex) of the centred sums
-        const double ox = d.lx[idx] - zcx, oy = d.ly[idx] - zcy;
-        const double q = d.lmd[idx] / (ox * ox + oy * oy) * (PIX ? d.inv_sdx : 1.0);
+        const double ox = lx[idx] - zcx, oy = ly[idx] - zcy;
+        const double q = lmd[idx] / (ox * ox + oy * oy) * (PIX ? d.inv_sdx : 1.0);
         return make_float4((float)ox, (float)oy, (float)(q * ox), (float)(-(q * oy)));
     } else if constexpr (PREC == 0) {
-        const float ox = (float)(d.lx[idx] - zcx), oy = (float)(d.ly[idx] - zcy);
+        const float ox = (float)(lx[idx] - zcx), oy = (float)(ly[idx] - zcy);
         if constexpr (PIX)
-            return make_float4(ox, oy, (float)(d.lmd[idx] * d.inv_sdx),
-                               (float)(d.lmd[idx] * d.inv_sdy));
+            return make_float4(ox, oy, (float)(lmd[idx] * d.inv_sdx),
+                               (float)(lmd[idx] * d.inv_sdy));
         else
-            return make_float4(ox, oy, d.lmf[idx], d.lmf[idx]);
+            return make_float4(ox, oy, lmf[idx], lmf[idx]);
     } else {
-        return make_float4(d.lxf[idx], d.lyf[idx], d.lmf[idx], d.lmf[idx]);
+        return make_float4(lxf[idx], lyf[idx], lmf[idx], lmf[idx]);
     }
 }
 
 // Stage list positions [b0, b0+nb) of the cell's lens list into this wave's LDS slice.
 template <int SCHEME, int PREC>
-__device__ void stage(const LmDesc& d, int64_t ci, int64_t cj, int b0, int nb, double zcx,
+__device__ __forceinline__ void stage(const LmDesc& d, int64_t ci, int64_t cj, int b0, int nb, double zcx,
                       double zcy, typename Prec<PREC>::L* lb, int lane)
 {
     if (SCHEME == 0) {
         for (int s = lane; s < nb; s += 64) lb[s] = lens_value<PREC>(d, b0 + s, zcx, zcy);
     } else {
+        // 64 list positions at a time, whatever rows they fall in: one round of
+        // lens loads per 64 lenses instead of one per row
         const L1Cell c = l1_of(d, ci, cj);
-        int off = 0;
-        for (int r = 0; r <= 2 * d.H; ++r) {
-            int s, e;
-            near_row(d, c, r, s, e);
-            int lo = max(off, b0), hi = min(off + (e - s), b0 + nb);
-            for (int k = lo + lane; k < hi; k += 64)
-                lb[k - b0] = lens_value<PREC>(d, s + (k - off), zcx, zcy);
-            off += e - s;
+        for (int k0 = 0; k0 < nb; k0 += 64) {
+            const int pos = b0 + k0 + lane;
+            int off = 0, idx = 0;
+            auto row = [&](int r) {
+                int s, e;
+                near_row(d, c, r, s, e);
+                if (pos >= off) idx = s + (pos - off);
+                off += e - s;
+            };
+            if (d.H == 1) {
+#pragma unroll
+                for (int r = 0; r < 3; ++r) row(r);
+            } else {
+                for (int r = 0; r <= 2 * d.H; ++r) row(r);
+            }
+            if (k0 + lane < nb) lb[k0 + lane] = lens_value<PREC>(d, idx, zcx, zcy);
         }
     }
     wave_sync_lds();
@@ -548,15 +582,15 @@ template <int P>
 __device__ __forceinline__ void load_taylor(const LmDesc& d, int64_t ci, int64_t cj, float* ar,
                                             float* ai, float& a0r, float& a0i)
 {
-    const LmCoef& c = d.coef[cj * d.ncx + ci];
-    a0r = (float)c.a0r;
-    a0i = (float)c.a0i;
+    ConstP<LmCoef> c = (ConstP<LmCoef>)d.coef + (cj * d.ncx + ci);
+    a0r = (float)c->a0r;
+    a0i = (float)c->a0i;
     ar[0] = 0.f;
     ai[0] = 0.f;
 #pragma unroll
     for (int n = 1; n < P; ++n) {
-        ar[n] = c.a[2 * (n - 1)];
-        ai[n] = c.a[2 * (n - 1) + 1];
+        ar[n] = c->a[2 * (n - 1)];
+        ai[n] = c->a[2 * (n - 1) + 1];
     }
 }
 
@@ -575,46 +609,46 @@ __device__ __forceinline__ unsigned long long run_key(unsigned p, unsigned q)
     return (unsigned long long)p | ((unsigned long long)q << 32);
 }
 
-// A workgroup's LDS window on the map: biased origin (axb, ayb) and the
-// extent (wxe, wye) of its part inside the map (the origin lies in the map).
+// A workgroup's LDS window on the map: its origin (ax0, ay0) in map pixels and
+// the extent (wxe, wye) of its part inside the map (the origin lies in the map).
 struct Win {
-    unsigned axb, ayb, wxe, wye;
+    unsigned ax0, ay0, wxe, wye;
 };
 
-// Add n rays at biased pixel (p, q): inside the window's part of the map ->
-// LDS, outside the map -> n_out, else a global atomic.
-__device__ __forceinline__ void emit(const Hot& h, unsigned p, unsigned q, unsigned n,
+// Add n rays at pixel (wxi, wyi), relative to the window's origin (modulo
+// 2^32): inside the window's part of the map -> LDS, outside the map -> n_out,
+// else a global atomic.
+__device__ __forceinline__ void emit(const Hot& h, unsigned wxi, unsigned wyi, unsigned n,
                                      const Win& w, unsigned* win, unsigned& nout)
 {
-    const unsigned wxi = p - w.axb, wyi = q - w.ayb;
     if ((wxi < w.wxe) & (wyi < w.wye)) {
         atomicAdd(&win[__umul24(wyi, (unsigned)h.wx) + wxi], n);
         return;
     }
-    const unsigned pm = p - kBias, qm = q - kBias;
+    const unsigned pm = wxi + w.ax0, qm = wyi + w.ay0;
     if ((pm >= (unsigned)h.snx) | (qm >= (unsigned)h.sny))
         nout += n;
     else
-        atomicAdd(&h.counts[(int64_t)qm * h.snx + pm], (unsigned long long)n);
+        atomicAdd(&h.counts[(uint64_t)qm * (unsigned)h.snx + pm], (unsigned long long)n);
 }
 
-// Lanes whose row lies outside the shot rectangle (row_ok false) keep runs like
-// every lane but never emit them, so the per-ray path needs no lane mask.  col
-// is the unit-local column of the ray (rays are pushed column by column).
-// (p, q) is the pixel less the lane's row base (bx, by), which is the same for
-// all of the lane's rays, so runs compare the offsets and a run adds the base
-// only when it is emitted.
+// Lanes whose row lies outside the shot rectangle (row_ok false)
+// keep runs like every lane but add runs of no rays, so the per-ray path needs
+// no lane mask.  col is the unit-local column of the ray (rays are pushed
+// column by column).  (p, q) is the pixel less the lane's row base, which is
+// the same for all of the lane's rays, so runs compare the offsets and a run
+// adds the base, less the window's origin (bxw, byw), only when it is emitted.
 __device__ __forceinline__ void run_push(const Hot& h, Run& r, unsigned p, unsigned q, int col,
-                                         unsigned bx, unsigned by, const Win& w, unsigned* win,
+                                         unsigned bxw, unsigned byw, const Win& w, unsigned* win,
                                          unsigned& nout, bool row_ok)
 {
-    // (a unit starts with an empty run at an arbitrary key; a run of length 0
-    // is never emitted, and one whose rays match that key names their pixel)
+    // (a unit starts with an empty run of the key that names biased pixel (0,
+    // 0), outside every map; a run of no rays adds nothing wherever it lands)
     const unsigned long long key = run_key(p, q);
     if (key != r.key) {
         // one divergent region for every lane whose run ends
-        const unsigned n = row_ok ? (unsigned)(col - r.start) : 0u;
-        if (n) emit(h, (unsigned)r.key + bx, (unsigned)(r.key >> 32) + by, n, w, win, nout);
+        emit(h, (unsigned)r.key + bxw, (unsigned)(r.key >> 32) + byw,
+             row_ok ? (unsigned)(col - r.start) : 0u, w, win, nout);
         r.key = key;
         r.start = col;
     }
@@ -622,20 +656,20 @@ __device__ __forceinline__ void run_push(const Hot& h, Run& r, unsigned p, unsig
 
 // End of a unit (col_end = unit-local column after its last ray): lanes whose
 // pending runs all name one pixel add it once.
-__device__ __forceinline__ void run_flush(const Hot& h, const Run& r, int col_end, unsigned bx,
-                                          unsigned by, const Win& w, unsigned* win,
+__device__ __forceinline__ void run_flush(const Hot& h, const Run& r, int col_end, unsigned bxw,
+                                          unsigned byw, const Win& w, unsigned* win,
                                           unsigned& nout, int lane, bool row_ok)
 {
-    const unsigned n = (unsigned)(col_end - r.start);
-    const unsigned rp = (unsigned)r.key + bx, rq = (unsigned)(r.key >> 32) + by;
-    bool act = row_ok && n > 0;
+    const unsigned n = row_ok ? (unsigned)(col_end - r.start) : 0u;
+    const unsigned rp = (unsigned)r.key + bxw, rq = (unsigned)(r.key >> 32) + byw;
+    const bool act = n > 0;
     unsigned long long am = __ballot(act);
     if (am) {
         int first = __builtin_ctzll(am);
         unsigned p0 = __shfl(rp, first, 64), q0 = __shfl(rq, first, 64);
         unsigned long long diff = __ballot(act && (rp != p0 || rq != q0));
         if (diff == 0) {
-            unsigned tot = wave_sum_u32(act ? n : 0u);
+            unsigned tot = wave_sum_u32(n);
             if (lane == first) emit(h, p0, q0, tot, w, win, nout);
         } else if (act) {
             emit(h, rp, rq, n, w, win, nout);
@@ -845,40 +879,6 @@ __device__ __forceinline__ void row_base_px(const Row<PREC, P, FOLD>& rw, unsign
 
 // --------------------------------------------------------------- units
 
-// Scalar (SMEM) loads of wave-uniform table entries.
-typedef const __attribute__((address_space(4))) float* ConstF;
-
-// One lens (row offset dy, mass m; called with dy = y_k - y, so that by holds
-// negated y sums) against the NR rays of a lane from its
-// table row (dx^2 and m dx per column): pair2 for all columns, staged so that
-// the reciprocals issue back to back instead of each right before its use.
-template <int NR, class T>
-__device__ __forceinline__ void lens_pairs(const T* row, T dy, T m, T* bx, T* by)
-{
-    const T dy2 = dy * dy;
-    const T mdy = m * dy;
-    T r2[NR], md[NR], rr[NR / 2];
-#pragma unroll
-    for (int c = 0; c < NR; ++c) {
-        r2[c] = row[c] + dy2;
-        md[c] = row[NR + c];
-    }
-#pragma unroll
-    for (int c = 0; c < NR; c += 2) rr[c / 2] = r2[c] * r2[c + 1];
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int c = 0; c < NR / 2; ++c) rr[c] = recip(rr[c]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int c = 0; c < NR; c += 2) {
-        const T wa = rr[c / 2] * r2[c + 1], wb = rr[c / 2] * r2[c];
-        bx[c] = fma(md[c], wa, bx[c]);
-        by[c] = fma(mdy, wa, by[c]);
-        bx[c + 1] = fma(md[c + 1], wb, bx[c + 1]);
-        by[c + 1] = fma(mdy, wb, by[c + 1]);
-    }
-}
-
 // Centred near sums.  With delta the ray's offset from the level-2 cell centre
 // and delta_k a near lens's, the lens deflects the ray by m (delta - delta_k) /
 // |delta - delta_k|^2; as complex numbers its change from the cell centre is
@@ -888,31 +888,92 @@ __device__ __forceinline__ void lens_pairs(const T* row, T dy, T m, T* bx, T* by
 // d_k = sum_k c_k conj(d_k) / |d_k|^2, while the deflection of the centre
 // itself is summed once per cell in FP64 (k_near_centre).  Every FP32 term is
 // then small (of order m |delta| / |delta_k|^2 instead of m / |delta_k|), so
-// its rounding is too.  One lens (e = y_k - y; the row holds dx^2, c_r dx and
-// c_i dx per column) against the NR rays of a lane, two columns sharing one
-// reciprocal as in lens_pairs:
+// its rounding is too.  With the column offset dx and e = y_k - y (c = c_r + i c_i):
 //   S_r += (c_r dx - c_i e) w,  S_i += (c_i dx + c_r e) w,  w = 1 / |d|^2.
-template <int NR, class T>
-__device__ __forceinline__ void lens_pairs_c(const T* row, T e, T cr, T ci, T* sr, T* si)
+
+// The nk lenses of the wave's table (rows dx^2 and m dx per column, or for the
+// centred sums dx^2, c_r dx and c_i dx) against the NR rays of a lane, added to
+// bx, by (by negated: row offsets are y_k - y); columns 2m and 2m + 1 share a
+// reciprocal as in pair2.
+//
+// Bound: vector issue.  A SIMD runs the vector instructions of two of its waves
+// at a time, four cycles each (2.07 cycles per instruction with every wave
+// ready), so its four waves fill it only while two of them are always ready:
+// the table reads must not be waited for.  A lens is therefore taken in steps of
+// S columns, and each step's table entries are read one step ahead, behind the
+// products and in front of the reciprocals of the step before (the last step
+// re-reads the last lens).  S = 8 in FP32 and 4 where an entry is wider (centred
+// sums, FP64) keeps both steps' entries within the registers of the waves per
+// SIMD of MinWaves.  And once its waves have mixed FP32 reciprocals into their
+// streams, a SIMD falls back to one instruction at a time: 8 reciprocals and 72
+// multiplies and FMAs per wave take 331 cycles, or 221 (8.3 per reciprocal and
+// 2.07 for the rest make 215) when the wave raises its priority around the
+// reciprocals.  Measured, shooting kernel before and after all of this: Table 1
+// band (centred) 120.3 and 113.3 ms, 110-lens lists (FP64) 51.5 and 47.5 ms, a
+// 4e11-ray band at paper scale 480 and 473 ms (484 without the priority).
+template <int PREC, int NR, class L, class T>
+__device__ __forceinline__ void lens_loop(const T* tb, const L* lb, int nk, T py, T* bx, T* by)
 {
-    const T e2 = e * e;
-    const T cie = ci * e, cre = cr * e;
-    T r2[NR], rr[NR / 2];
+    constexpr bool CENT = PREC == kPrecCentred;
+    constexpr int TW = tab_width(PREC);
+    constexpr int kS = CENT || sizeof(T) == 8 ? 4 : 8;
+    constexpr int S = NR < kS ? NR : kS;
+    constexpr int H = NR / S;          // steps per lens
+    constexpr int U = H > 1 ? 1 : 2;   // lenses per iteration: the two buffers alternate
+    static_assert(H == 1 || H % 2 == 0, "steps alternate between two buffers");
+    T buf[2][TW * S];
+    auto load = [&](T* b, const T* row) {
 #pragma unroll
-    for (int c = 0; c < NR; ++c) r2[c] = row[c] + e2;
+        for (int t = 0; t < TW; ++t)
 #pragma unroll
-    for (int c = 0; c < NR; c += 2) rr[c / 2] = r2[c] * r2[c + 1];
-    __builtin_amdgcn_sched_barrier(0);
+            for (int c = 0; c < S; ++c) b[t * S + c] = row[t * NR + c];
+    };
+    auto step = [&](const T* b, int h, T e2, T f0, T f1, T* nb, const T* nrow) {
+        T r2[S], rr[S / 2];
 #pragma unroll
-    for (int c = 0; c < NR / 2; ++c) rr[c] = recip(rr[c]);
-    __builtin_amdgcn_sched_barrier(0);
+        for (int c = 0; c < S; ++c) r2[c] = b[c] + e2;
 #pragma unroll
-    for (int c = 0; c < NR; c += 2) {
-        const T wa = rr[c / 2] * r2[c + 1], wb = rr[c / 2] * r2[c];
-        sr[c] = fma(row[NR + c] - cie, wa, sr[c]);
-        si[c] = fma(row[2 * NR + c] + cre, wa, si[c]);
-        sr[c + 1] = fma(row[NR + c + 1] - cie, wb, sr[c + 1]);
-        si[c + 1] = fma(row[2 * NR + c + 1] + cre, wb, si[c + 1]);
+        for (int c = 0; c < S; c += 2) rr[c / 2] = r2[c] * r2[c + 1];
+        __builtin_amdgcn_sched_barrier(0);
+        load(nb, nrow);
+        __builtin_amdgcn_sched_barrier(0);
+        if (sizeof(T) == 4) __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+        for (int c = 0; c < S / 2; ++c) rr[c] = recip(rr[c]);
+        if (sizeof(T) == 4) __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < S; ++c) {
+            const int o = h * S + c;
+            const T w = rr[c / 2] * r2[c ^ 1];
+            if constexpr (CENT) {
+                bx[o] = fma(b[S + c] - f0, w, bx[o]);
+                by[o] = fma(b[2 * S + c] + f1, w, by[o]);
+            } else {
+                bx[o] = fma(b[S + c], w, bx[o]);
+                by[o] = fma(f0, w, by[o]);
+            }
+        }
+    };
+    L Lk = lb[0];
+    load(buf[0], tb);
+    for (int k = 0; k < nk; k += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u > 0 && k + u >= nk) break;  // wave-uniform
+            const int kn = min(k + u + 1, nk - 1);
+            const T e = Lk.y - py;
+            const T e2 = e * e;
+            // plain: m e; centred: c_i e and c_r e
+            const T f0 = Lk.w * e, f1 = CENT ? Lk.z * e : T(0);
+            Lk = lb[kn];
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const T* nrow = h + 1 < H ? tb + (k + u) * TW * NR + (h + 1) * S
+                                          : tb + kn * TW * NR;
+                step(buf[(u * H + h) & 1], h, e2, f0, f1, buf[(u * H + h + 1) & 1], nrow);
+            }
+        }
     }
 }
 
@@ -971,15 +1032,35 @@ __device__ __forceinline__ void centre_bases(const LmDesc& d, const LmCoef& cf,
     rw.ubyb = __builtin_fma(-cf.n0y, d.inv_sdy, rw.ubyb);
 }
 
-// Row-polynomial start values of the NR rays of a lane from the wave-uniform
-// column powers (scalar loads), one power at a time so that only NR of them
-// are live in scalar registers; px gets the column offsets (first powers).
-// CENT: ax, ay hold the centred sums S on entry, and the start is added on top
-// of their change conj(delta S) (centred_first; the table's row LM_PTAB_POW
-// holds the column offsets times sdx / sdy).
+// Powers dx .. dx^D of a column group's offsets into the wave's LDS slice,
+// tb[k NR + c] = dx_c^(k+1), by the lanes of the first NR (pxl: the offset of
+// column lane mod NR); centred sums: and a row of dx sdx / sdy.
+template <int PREC, int P, bool FOLD, int NR>
+__device__ __forceinline__ void stage_powers(const LmDesc& d, typename Prec<PREC>::T pxl,
+                                             typename Prec<PREC>::T* tb, int lane)
+{
+    using T = typename Prec<PREC>::T;
+    constexpr int D = Row<PREC, P, FOLD>::D;
+    if (lane < NR) {
+        T pw[D];
+        col_powers<D>(pxl, pw);
+#pragma unroll
+        for (int k = 0; k < D; ++k) tb[k * NR + lane] = pw[k];
+        if constexpr (PREC == kPrecCentred) tb[D * NR + lane] = pix_ratio(d) * pw[0];
+    }
+    wave_sync_lds();
+}
+
+// Row-polynomial start values of the NR rays of a lane from the staged column
+// powers (LDS broadcasts), one power at a time so that only NR of them are
+// live.  The powers are the same for all rows, but come as vector registers: a
+// VOP2 or VOP3 instruction with a scalar operand issues every ~4.5 cycles per
+// SIMD, one with vector operands every ~2.2, and the start is 2 D of a ray's
+// instructions.  CENT: ax, ay hold the centred sums S on entry, and the start
+// is added on top of their change conj(delta S) (centred_first).
 template <bool NEGX, bool NEGY, int PREC, int P, bool FOLD, int NR, bool CENT = false>
-__device__ __forceinline__ void table_start(ConstF tab, int R, const Row<PREC, P, FOLD>& rw,
-                                            typename Prec<PREC>::T* px,
+__device__ __forceinline__ void table_start(const typename Prec<PREC>::T* tb,
+                                            const Row<PREC, P, FOLD>& rw,
                                             typename Prec<PREC>::T* ax,
                                             typename Prec<PREC>::T* ay)
 {
@@ -990,13 +1071,11 @@ __device__ __forceinline__ void table_start(ConstF tab, int R, const Row<PREC, P
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < NR; ++c) {
-            const T pk = tab[k * (R + LM_PTAB_PAD) + c];
+            const T pk = tb[k * NR + c];
             if (k == 0) {
-                px[c] = pk;
                 if constexpr (CENT) {
                     // the centred sums S on entry (ax = S_r, ay = S_i)
-                    const T pkr = tab[LM_PTAB_POW * (R + LM_PTAB_PAD) + c];
-                    centred_first<P, FOLD>(rw, pk, pkr, ax[c], ay[c], ax[c], ay[c]);
+                    centred_first<P, FOLD>(rw, pk, tb[D * NR + c], ax[c], ay[c], ax[c], ay[c]);
                 } else {
                     ray_start_first<NEGX, NEGY, PREC, P, FOLD>(rw, pk, ax[c], ay[c]);
                 }
@@ -1006,13 +1085,14 @@ __device__ __forceinline__ void table_start(ConstF tab, int R, const Row<PREC, P
         }
     }
     __builtin_amdgcn_sched_barrier(0);
+    wave_sync_lds();
 }
 
 // Columns [c_lo, c_hi) of cell ci are computed (c_lo even, so columns 2m and
 // 2m + 1 share a group); rays of columns >= c_beg are counted.  LAY: the LDS
 // layout (near-list block, table block).
 template <int SCHEME, int PREC, int NR, int P, bool FOLD, int LAY>
-__device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_lo, int64_t c_beg,
+__device__ __forceinline__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_lo, int64_t c_beg,
                              int64_t c_hi, int64_t j, bool row_ok, const Win& w,
                              unsigned* win, typename Prec<PREC>::L* lb,
                              typename Prec<PREC>::T* tb, int lane, unsigned& nout)
@@ -1027,7 +1107,6 @@ __device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_
     float ar[P > 1 ? P : 1], ai[P > 1 ? P : 1], a0r = 0.f, a0i = 0.f;
     if (SCHEME == 1) load_taylor<P>(d, ci, cj, ar, ai, a0r, a0i);
     const float zcxf = cell_cxf(d, ci), zcyf = cell_cyf(d, cj);
-    const float h_hxh = d.hxh, h_hxl = d.hxl;
 
     // the lane's ray row
     Row<PREC, P, FOLD> rw;
@@ -1044,12 +1123,12 @@ __device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_
     const int nblk = (count + kCap - 1) / kCap;
     if (nblk == 1) stage<SCHEME, PREC>(d, ci, cj, 0, count, zcx, zcy, lb, lane);
 
-    Run run{run_key(kBias - 2, kBias - 2), (int)(c_beg - c_lo)};
     unsigned bxr, byr;
     row_base_px(rw, bxr, byr);
+    Run run{run_key(0u - bxr, 0u - byr), (int)(c_beg - c_lo)};
+    const unsigned bxw = bxr - (w.ax0 + kBias), byw = byr - (w.ay0 + kBias);
     for (int64_t c0 = c_lo; c0 < c_hi; c0 += NR) {
         constexpr int D = Row<PREC, P, FOLD>::D;
-        static_assert(D <= LM_PTAB_POW, "column table holds too few powers");
         // the table path carries the y sums negated (lens offsets y_k - y):
         // the row coefficients -gy and the FP64 binning take the sign for free
         constexpr bool NEGY = UseTab<SCHEME, PREC>::value;
@@ -1057,7 +1136,14 @@ __device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_
         // (the centred sums negate theirs when the start is added)
         constexpr bool NEGX = NEGY;
         constexpr int TW = tab_width(PREC);
+        // the rebased paths share a table of column powers, which takes the place
+        // of the lens table before it is built
+        constexpr bool POW = UseTab<SCHEME, PREC>::value && PREC != 1;
+        static_assert(!POW || (D + CENT) * NR <= kTabCh * TW * NR, "powers exceed the table");
         T px[NR], ax[NR], ay[NR], kx[NR], ky[NR];
+        T pxl = 0;  // offset of this lane's column in the wave's tables: NR divides 64
+        if constexpr (UseTab<SCHEME, PREC>::value)
+            pxl = column_offset<PREC>(d, c0 + (lane & (NR - 1)), ci);
         if constexpr (CENT) {
             // the sums S start at zero; the row-polynomial start is added after
             // the lenses (table_start on the sums' change)
@@ -1066,10 +1152,9 @@ __device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_
                 ax[c] = 0;
                 ay[c] = 0;
             }
-        } else if constexpr (PREC == 0) {
-            // wave-uniform column offsets and their powers from the map's table
-            table_start<NEGX, NEGY, PREC, P, FOLD, NR>((ConstF)(d.ptab + (c0 - ci * (int64_t)R)),
-                                                       R, rw, px, ax, ay);
+        } else if constexpr (POW) {
+            stage_powers<PREC, P, FOLD, NR>(d, pxl, tb, lane);
+            table_start<NEGX, NEGY, PREC, P, FOLD, NR>(tb, rw, ax, ay);
         } else {
 #pragma unroll
             for (int c = 0; c < NR; ++c) {
@@ -1096,12 +1181,6 @@ __device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_
                 by[c] = SCHEME == 0 ? T(0) : ay[c];
             }
             if constexpr (UseTab<SCHEME, PREC>::value) {
-                // this lane's column in the table build: NR divides 64
-                T pxl;
-                if constexpr (PREC == 0 || CENT)
-                    pxl = local_offset(c0 + (lane & (NR - 1)), ci, R, h_hxh, h_hxl);
-                else
-                    pxl = column_offset<PREC>(d, c0 + (lane & (NR - 1)), ci);
                 for (int k0 = 0; k0 < nb; k0 += kTabCh) {
                     // wave-uniform count: scalar loop control
                     const int nk = __builtin_amdgcn_readfirstlane(min(kTabCh, nb - k0));
@@ -1116,26 +1195,7 @@ __device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_
                         if constexpr (CENT) tb[k * TW * NR + 2 * NR + c] = L.w * dx;
                     }
                     wave_sync_lds();
-                    // two lenses per step: their LDS reads share base addresses
-                    int k = 0;
-                    for (; k + 2 <= nk; k += 2) {
-                        const auto L0 = lb[k0 + k], L1 = lb[k0 + k + 1];
-                        if constexpr (CENT) {
-                            lens_pairs_c<NR>(tb + k * TW * NR, L0.y - py, L0.z, L0.w, bx, by);
-                            lens_pairs_c<NR>(tb + (k + 1) * TW * NR, L1.y - py, L1.z, L1.w, bx,
-                                             by);
-                        } else {
-                            lens_pairs<NR>(tb + k * TW * NR, L0.y - py, L0.w, bx, by);
-                            lens_pairs<NR>(tb + (k + 1) * TW * NR, L1.y - py, L1.w, bx, by);
-                        }
-                    }
-                    if (k < nk) {
-                        const auto L = lb[k0 + k];
-                        if constexpr (CENT)
-                            lens_pairs_c<NR>(tb + k * TW * NR, L.y - py, L.z, L.w, bx, by);
-                        else
-                            lens_pairs<NR>(tb + k * TW * NR, L.y - py, L.w, bx, by);
-                    }
+                    lens_loop<PREC, NR>(tb, lb + k0, nk, py, bx, by);
                     wave_sync_lds();
                 }
             } else {
@@ -1162,9 +1222,9 @@ __device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_
         }
         if constexpr (CENT) {
             // the change conj(delta S) of the near deflection, then the
-            // row-polynomial start on top of it (and the column offsets)
-            table_start<NEGX, NEGY, PREC, P, FOLD, NR, true>(
-                (ConstF)(d.ptab + (c0 - ci * (int64_t)R)), R, rw, px, ax, ay);
+            // row-polynomial start on top of it
+            stage_powers<PREC, P, FOLD, NR>(d, pxl, tb, lane);
+            table_start<NEGX, NEGY, PREC, P, FOLD, NR, true>(tb, rw, ax, ay);
         }
         const int ncol = (int)min((int64_t)NR, c_hi - c0);
         const int cfirst = (int)max((int64_t)0, c_beg - c0);
@@ -1176,7 +1236,7 @@ __device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_
                 unsigned p, q;
                 ray_bin<PREC, P, FOLD>(h, rw, ar, ai, a0r, a0i, zcxf, zcyf, px[c],
                                        NEGX ? -ax[c] : ax[c], NEGY ? -ay[c] : ay[c], p, q);
-                run_push(h, run, p, q, col0 + c, bxr, byr, w, win, nout, row_ok);
+                run_push(h, run, p, q, col0 + c, bxw, byw, w, win, nout, row_ok);
             }
         } else {
 #pragma unroll
@@ -1186,47 +1246,53 @@ __device__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_
                     ray_bin<PREC, P, FOLD>(h, rw, ar, ai, a0r, a0i, zcxf, zcyf, px[c],
                                            NEGX ? -ax[c] : ax[c], NEGY ? -ay[c] : ay[c], p,
                                            q);
-                    run_push(h, run, p, q, col0 + c, bxr, byr, w, win, nout, row_ok);
+                    run_push(h, run, p, q, col0 + c, bxw, byw, w, win, nout, row_ok);
                 }
             }
         }
     }
-    run_flush(h, run, (int)(c_hi - c_lo), bxr, byr, w, win, nout, lane, row_ok);
+    run_flush(h, run, (int)(c_hi - c_lo), bxw, byw, w, win, nout, lane, row_ok);
 }
 
 // Window origin of a tile: the pixel of the image of its centre cell's centre
 // (macro map, far field and near lenses, FP64), less half the window, moved
 // into the map as far as the window allows (no window bin outside the map is
 // ever written, and none of its area is spent outside the map where the
-// map allows).
+// map allows).  The cell's lenses are spread over the lanes and their sums
+// added across the wave: every wave of the workgroup finds the same origin.
 template <int SCHEME>
-__device__ __forceinline__ void tile_anchor(const LmDesc& d, int64_t cib, int64_t cjb, int& ax0,
-                                            int& ay0)
+__device__ __forceinline__ void tile_anchor(const LmDesc& d, int64_t cib, int64_t cjb, int lane,
+                                            int& ax0, int& ay0)
 {
     int64_t cic = min(cib + d.G / 2, d.ncx - 1), cjc = min(cjb + d.G / 2, d.ncy - 1);
     double ubx, uby;
     cell_base<SCHEME>(d, cic, cjc, ubx, uby);
     const double zcx = cell_cx(d, cic), zcy = cell_cy(d, cjc);
     double sx = 0.0, sy = 0.0;
-    auto add = [&](int idx) {
-        const double dx = zcx - d.lx[idx], dy = zcy - d.ly[idx];
-        const double r2 = dx * dx + dy * dy;
-        if (r2 > 0.0) {
-            const double w = d.lmd[idx] / r2;
-            sx += dx * w;
-            sy += dy * w;
+    auto add = [&](int s, int e) {
+        for (int idx = s + lane; idx < e; idx += 64) {
+            const double dx = zcx - global_ptr(d.lx)[idx], dy = zcy - global_ptr(d.ly)[idx];
+            const double r2 = dx * dx + dy * dy;
+            if (r2 > 0.0) {
+                const double w = global_ptr(d.lmd)[idx] / r2;
+                sx += dx * w;
+                sy += dy * w;
+            }
         }
     };
-    // the cell's lens list in list order
     if (SCHEME == 0) {
-        for (int k = 0; k < (int)d.nlens; ++k) add(k);
+        add(0, (int)d.nlens);
     } else {
         const L1Cell c = l1_of(d, cic, cjc);
         for (int r = 0; r <= 2 * d.H; ++r) {
             int s, e;
             near_row(d, c, r, s, e);
-            for (int idx = s; idx < e; ++idx) add(idx);
+            add(s, e);
         }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        sx += __shfl_xor(sx, o, 64);
+        sy += __shfl_xor(sy, o, 64);
     }
     ubx -= sx * d.inv_sdx;
     uby -= sy * d.inv_sdy;
@@ -1235,17 +1301,17 @@ __device__ __forceinline__ void tile_anchor(const LmDesc& d, int64_t cib, int64_
     if (fy != fy) fy = 0.0;
     fx = fmin(fmax(fx, 0.0), (double)max(d.snx - d.wx, 0));
     fy = fmin(fmax(fy, 0.0), (double)max(d.sny - d.wy, 0));
-    ax0 = (int)fx;
-    ay0 = (int)fy;
+    ax0 = __builtin_amdgcn_readfirstlane((int)fx);
+    ay0 = __builtin_amdgcn_readfirstlane((int)fy);
 }
 
 template <int SCHEME, int PREC, int NR, int P, int LAY>
-__device__ void process_tile(const LmDesc& d, int64_t t, int ax0, int ay0, unsigned* win,
+__device__ __forceinline__ void process_tile(const LmDesc& d, int64_t t, int ax0, int ay0, unsigned* win,
                              typename Prec<PREC>::L* lb, typename Prec<PREC>::T* tb, int wave,
                              int lane)
 {
-    const Win w{(unsigned)ax0 + kBias, (unsigned)ay0 + kBias,
-                (unsigned)min(d.wx, d.snx - ax0), (unsigned)min(d.wy, d.sny - ay0)};
+    const Win w{(unsigned)ax0, (unsigned)ay0, (unsigned)min(d.wx, d.snx - ax0),
+                (unsigned)min(d.wy, d.sny - ay0)};
     // fewer than 2^31 tiles per launch (checked on the host)
     const int ntx = (int)d.ntx;
     const int64_t tx = (int)t % ntx, ty = (int)t / ntx;
@@ -1270,7 +1336,7 @@ __device__ void process_tile(const LmDesc& d, int64_t t, int ax0, int ay0, unsig
         // centred sums: a cell with a near lens close to its centre (n0 NaN,
         // wave-uniform) sums its near lenses plainly
         constexpr int PU = PREC == kPrecCentred ? 0 : PREC;
-        if (PREC == kPrecCentred && !__builtin_isnan(d.coef[cj * d.ncx + ci].n0x)) {
+        if (PREC == kPrecCentred && !__builtin_isnan(((ConstP<LmCoef>)d.coef)[cj * d.ncx + ci].n0x)) {
             if (d.fold)
                 process_unit<SCHEME, PREC, NR, P, true, LAY>(d, ci, cj, c_lo, c_beg, c_hi, j,
                                                              row_ok, w, win, lb, tb, lane, nout);
@@ -1286,7 +1352,7 @@ __device__ void process_tile(const LmDesc& d, int64_t t, int ax0, int ay0, unsig
         }
     }
     unsigned tot = wave_sum_u32(nout);
-    if (lane == 0 && tot) atomicAdd(d.n_out, (unsigned long long)tot);
+    if (lane == 0 && tot) atomicAdd(global_ptr(d.n_out), (unsigned long long)tot);
 }
 
 __device__ __forceinline__ void flush_window(const LmDesc& d, unsigned* win, int ax0, int ay0,
@@ -1297,7 +1363,7 @@ __device__ __forceinline__ void flush_window(const LmDesc& d, unsigned* win, int
         unsigned v = win[b];
         if (v) {
             int64_t p = (int64_t)ax0 + b % d.wx, q = (int64_t)ay0 + b / d.wx;
-            atomicAdd(&d.counts[q * d.snx + p], (unsigned long long)v);
+            atomicAdd(&global_ptr(d.counts)[q * d.snx + p], (unsigned long long)v);
             win[b] = 0u;
         }
     }
@@ -1307,8 +1373,15 @@ __device__ __forceinline__ void flush_window(const LmDesc& d, unsigned* win, int
 
 template <int SCHEME, int PREC, int NR, int P>
 __global__ __launch_bounds__(kWG)
-__attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot_map(LmDesc d)
+__attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot_map(LmDesc)
 {
+    // the descriptor, the kernel's only argument, read where it is used: as an
+    // argument by name its fields are loaded at the start and kept, which spills
+    // ~75 scalar registers into vector lanes and, at 16 rays per lane, vector
+    // registers to scratch
+    ConstP<LmDesc> dp = (ConstP<LmDesc>)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(dp));
+    const LmDesc& d = *(const LmDesc*)dp;
     __shared__ unsigned win[window_bins(PREC, 0, NR)];
     __shared__ typename Prec<PREC>::L lens[LM_WAVES][Cap<SCHEME, 0>::value];
     __shared__ __align__(16) typename Prec<PREC>::T
@@ -1321,7 +1394,7 @@ __attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot
     // fewer than 2^31 tiles per map (checked on the host)
     const int64_t tx = (int)t % (int)d.ntx, ty = (int)t / (int)d.ntx;
     int ax0, ay0;
-    tile_anchor<SCHEME>(d, (d.tcx0 + tx) * d.G, (d.tcy0 + ty) * d.G, ax0, ay0);
+    tile_anchor<SCHEME>(d, (d.tcx0 + tx) * d.G, (d.tcy0 + ty) * d.G, lane, ax0, ay0);
     __syncthreads();
     process_tile<SCHEME, PREC, NR, P, 0>(d, t, ax0, ay0, win, lens[wave], tab[wave], wave, lane);
     __syncthreads();
@@ -1364,7 +1437,7 @@ __attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot
         // fewer than 2^31 tiles per map (checked on the host)
         const int64_t tx = (int)t % (int)d.ntx, ty = (int)t / (int)d.ntx;
         int ax0, ay0;
-        tile_anchor<SCHEME>(d, (d.tcx0 + tx) * d.G, (d.tcy0 + ty) * d.G, ax0, ay0);
+        tile_anchor<SCHEME>(d, (d.tcx0 + tx) * d.G, (d.tcy0 + ty) * d.G, lane, ax0, ay0);
         process_tile<SCHEME, PREC, NR, P, LAY>(d, t, ax0, ay0, win, lens[wave], tab[wave], wave,
                                                lane);
         __syncthreads();

@@ -35,9 +35,6 @@ constexpr int window_bins(int prec, int layout, int rays_per_lane)
     return kLayWin[layout] -
            (prec == kPrecCentred ? LM_WAVES * kLayTab[layout] * rays_per_lane : 0);
 }
-#define LM_PTAB_PAD 64     // column-offset table entries past R (last column group)
-#define LM_PTAB_POW 6      // powers dx .. dx^6 per column (row polynomials, P <= 7)
-#define LM_PTAB_ROWS 7     // and a row of dx sdx / sdy (the centred sums' y change)
 
 // Allocation-free peak statistics: limits and layout of the per-device scratch
 // array (tracks, column bins, two histograms; each part 256-byte aligned).
@@ -110,8 +107,6 @@ struct LmDesc {
     const int32_t* lJ;
     const int32_t* cell_start;     // CSR over the padded level-1 grid
     const LmCoef* coef;            // [ncy][ncx]
-    const float* ptab;             // [LM_PTAB_ROWS][R + LM_PTAB_PAD] column offsets of a
-                                   // level-2 cell and their powers
     double* l1exp;                 // [n1y nby][n1x nbx][Q] level-1 series per box, complex
     unsigned long long* counts;    // [sny][snx]
     unsigned long long* n_out;
@@ -121,7 +116,6 @@ struct LmDesc {
 // The rectangle sheet's holomorphic part added to every level-2 cell's
 // coefficients (after the far-field kernels).
 int lm_launch_sheet(const LmDesc& d, int terms, LmCoef* coef, void* stream);
-int lm_launch_ptab(const LmDesc& d, float* out, int n, void* stream);
 int lm_launch_coeffs(const LmDesc& d, int precision, int terms, int64_t ci0, int64_t cj0,
                      int64_t nci, int64_t ncj, LmCoef* out, void* stream);
 // Hierarchical far field: level-1 series (d.Q terms) into d.l1exp, then the

@@ -8,7 +8,6 @@
 //                 FP32 rate on gfx950).
 //  k_l1_expand    hierarchical far field (optional): series per level-1 cell,
 //  k_l1_shift     re-expanded about every level-2 centre.
-//  k_ptab         the column-offset table of the shooting kernels.
 //  k_sum_u64, k_fill_u64   reductions and fills of count buffers.
 //
 // The shooting kernels (k_shoot_map: one workgroup per tile of level-2 cells;
@@ -113,22 +112,6 @@ __global__ __launch_bounds__(kWG) void k_coeffs(LmDesc d, int64_t ci0, int64_t c
             o.a[2 * (n - 1)] = n < P ? (float)ar[n < P ? n : 0] : 0.f;
             o.a[2 * (n - 1) + 1] = n < P ? (float)ai[n < P ? n : 0] : 0.f;
         }
-    }
-}
-
-// Column offsets dx = local_offset(l) of a level-2 cell and their powers:
-// out[k n + l] = dx^(k+1), k < LM_PTAB_POW, and out[LM_PTAB_POW n + l] =
-// dx sdx / sdy, l = 0 .. n-1 (entries past R belong
-// to masked columns of the last group).
-__global__ void k_ptab(LmDesc d, float* __restrict__ out, int n)
-{
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l < n) {
-        float pw[LM_PTAB_POW];
-        col_powers<LM_PTAB_POW>(local_offset(l, 0, d.R, d.hxh, d.hxl), pw);
-#pragma unroll
-        for (int k = 0; k < LM_PTAB_POW; ++k) out[(int64_t)k * n + l] = pw[k];
-        out[(int64_t)LM_PTAB_POW * n + l] = pix_ratio(d) * pw[0];
     }
 }
 
@@ -564,14 +547,6 @@ int lm_launch_near_centre(const LmDesc& d, LmCoef* out, void* stream)
     if (n <= 0) return 0;
     hipLaunchKernelGGL(k_near_centre, dim3((unsigned)((n + kWG - 1) / kWG)), dim3(kWG), 0,
                        (hipStream_t)stream, d, out);
-    return (int)hipGetLastError();
-}
-
-int lm_launch_ptab(const LmDesc& d, float* out, int n, void* stream)
-{
-    if (n <= 0) return 0;
-    hipLaunchKernelGGL(k_ptab, dim3((unsigned)((n + kWG - 1) / kWG)), dim3(kWG), 0,
-                       (hipStream_t)stream, d, out, n);
     return (int)hipGetLastError();
 }
 
