@@ -13,10 +13,13 @@
 #include <fstream>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <numeric>
 #include <sstream>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "../../include/lensmap.h"
@@ -191,9 +194,149 @@ lm_status validate_geometry(const lm_geometry* g)
 
 }  // namespace
 
+// ============================================================ pinned staging
+
+namespace {
+
+// Pinned host memory the device writes results to, in lanes of two buffers, a
+// stream and two events: a reader fills one buffer while it empties the other.
+// A large read runs its lanes on threads of their own, since copying into fresh
+// pageable memory is slower per thread (10 GB/s) than the bus (57 GB/s).
+constexpr int kLanes = 8;
+constexpr size_t kLaneBytes = size_t(1) << 20;  // per buffer: 16 MiB a set
+
+struct Lane {
+    unsigned long long* buf[2] = {nullptr, nullptr};
+    hipStream_t s = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+};
+
+struct Stage {
+    int device = 0;
+    unsigned long long* mem = nullptr;
+    Lane lane[kLanes];
+    ~Stage()
+    {
+        for (Lane& l : lane) {
+            for (hipEvent_t e : l.ev)
+                if (e) (void)hipEventDestroy(e);
+            if (l.s) (void)hipStreamDestroy(l.s);
+        }
+        if (mem) (void)hipHostFree(mem);
+    }
+    hipError_t init(int dev)
+    {
+        device = dev;
+        void* p = nullptr;
+        hipError_t e = hipHostMalloc(&p, 2 * kLanes * kLaneBytes, hipHostMallocDefault);
+        if (e != hipSuccess) return e;
+        mem = static_cast<unsigned long long*>(p);
+        for (int k = 0; k < kLanes; ++k) {
+            Lane& l = lane[k];
+            for (int b = 0; b < 2; ++b) {
+                l.buf[b] = mem + (2 * k + b) * (kLaneBytes / 8);
+                e = hipEventCreateWithFlags(&l.ev[b], hipEventDisableTiming);
+                if (e != hipSuccess) return e;
+            }
+            e = hipStreamCreateWithFlags(&l.s, hipStreamNonBlocking);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+};
+
+// Sets not in use: at most kStagesKept of them, kept while any map lives and
+// freed with the last one.  A call takes a set for itself, so calls on several
+// threads never share one.
+constexpr size_t kStagesKept = 2;
+
+struct StagePool {
+    std::mutex mu;
+    Stage* kept[kStagesKept] = {nullptr, nullptr};
+    int64_t maps = 0;
+};
+
+StagePool& stage_pool()
+{
+    static StagePool* p = new StagePool;  // never destroyed: the HIP runtime may go first
+    return *p;
+}
+
+// A set for the current call on `device`, returned to the pool at its end.
+class StageUse {
+public:
+    explicit StageUse(int device)
+    {
+        StagePool& P = stage_pool();
+        {
+            std::lock_guard<std::mutex> lock(P.mu);
+            for (Stage*& k : P.kept)
+                if (k && k->device == device) {
+                    st_ = k;
+                    k = nullptr;
+                    return;
+                }
+        }
+        std::unique_ptr<Stage> s(new (std::nothrow) Stage);
+        if (s && s->init(device) == hipSuccess) {
+            st_ = s.release();
+        } else {
+            (void)hipGetLastError();  // the caller falls back on plain copies
+        }
+    }
+    ~StageUse()
+    {
+        if (!st_) return;
+        StagePool& P = stage_pool();
+        {
+            std::lock_guard<std::mutex> lock(P.mu);
+            if (P.maps > 0)
+                for (Stage*& k : P.kept)
+                    if (!k) {
+                        k = st_;
+                        return;
+                    }
+        }
+        delete st_;
+    }
+    StageUse(const StageUse&) = delete;
+    StageUse& operator=(const StageUse&) = delete;
+    Stage* operator->() const { return st_; }
+    explicit operator bool() const { return st_ != nullptr; }
+
+private:
+    Stage* st_ = nullptr;
+};
+
+// Counts the live maps; the kept sets go with the last one.
+struct MapCount {
+    MapCount()
+    {
+        StagePool& P = stage_pool();
+        std::lock_guard<std::mutex> lock(P.mu);
+        ++P.maps;
+    }
+    ~MapCount()
+    {
+        StagePool& P = stage_pool();
+        Stage* drop[kStagesKept] = {nullptr, nullptr};
+        {
+            std::lock_guard<std::mutex> lock(P.mu);
+            if (--P.maps == 0)
+                for (size_t k = 0; k < kStagesKept; ++k) std::swap(drop[k], P.kept[k]);
+        }
+        for (Stage* s : drop) delete s;
+    }
+    MapCount(const MapCount&) = delete;
+    MapCount& operator=(const MapCount&) = delete;
+};
+
+}  // namespace
+
 // ====================================================================== map
 
 struct lm_map {
+    MapCount counted;
     lm_geometry g{};
     int device = 0;
     double kappa = 0, gamma = 0, kappa_star = 0;
@@ -1004,17 +1147,129 @@ lm_status lm_sync(lm_map* m)
     return ok();
 }
 
+}  // extern "C"
+
+namespace {
+
+// What is read back: a window of the map (rows from q0, np columns from p0; the
+// whole map as one row) as counts or magnifications.
+struct ReadJob {
+    const unsigned long long* map;
+    int64_t snx, p0, q0, np;
+    int64_t n;  // entries
+    bool whole, mu;
+    double factor;
+    unsigned char* dst;
+};
+
+// Chunks k, k + step, .. of a job through one lane.
+hipError_t read_lane(const ReadJob& r, Lane& l, int64_t k, int64_t step)
+{
+    const int64_t ch = (int64_t)(kLaneBytes / 8);
+    const int64_t nk = ceil_div(r.n, ch);
+    auto issue = [&](int64_t c, int b) {
+        hipError_t e = (hipError_t)lm_launch_read_back(
+            r.map, r.snx, r.p0, r.q0, r.np, r.whole, r.mu, c * ch, std::min(ch, r.n - c * ch),
+            r.factor, l.buf[b], nullptr, l.s);
+        return e != hipSuccess ? e : hipEventRecord(l.ev[b], l.s);
+    };
+    hipError_t e = k < nk ? issue(k, 0) : hipSuccess;
+    for (int b = 0; e == hipSuccess && k < nk; k += step, b ^= 1) {
+        if (k + step < nk) e = issue(k + step, b ^ 1);
+        if (e == hipSuccess) e = hipEventSynchronize(l.ev[b]);
+        if (e == hipSuccess)
+            std::memcpy(r.dst + 8 * k * ch, l.buf[b], (size_t)std::min(ch, r.n - k * ch) * 8);
+    }
+    if (e != hipSuccess) (void)hipStreamSynchronize(l.s);  // nothing may write the lane later
+    return e;
+}
+
+// Runs a job on the device's idle streams (the caller has waited for the map's
+// work); a read of 4 MiB and more on one thread per lane it fills.
+hipError_t read_job(const ReadJob& r, Stage& st)
+{
+    const int64_t nk = ceil_div(r.n, (int64_t)(kLaneBytes / 8));
+    const int nt = (int)std::min<int64_t>(kLanes, nk / 2);
+    if (nt < 2) return read_lane(r, st.lane[0], 0, 1);
+    hipError_t err[kLanes];
+    std::thread th[kLanes];
+    int started = 1;  // lane 0 runs here
+    for (; started < nt; ++started) {
+        const int k = started;
+        try {
+            th[k] = std::thread([&r, &st, &err, k, nt] {
+                err[k] = hipSetDevice(st.device);
+                if (err[k] == hipSuccess) err[k] = read_lane(r, st.lane[k], k, nt);
+            });
+        } catch (const std::system_error&) {
+            break;  // no more threads: the rest runs here
+        }
+    }
+    err[0] = read_lane(r, st.lane[0], 0, nt);
+    for (int k = started; k < nt; ++k) err[k] = read_lane(r, st.lane[k], k, nt);
+    for (int k = 1; k < started; ++k) th[k].join();
+    for (int k = 0; k < nt; ++k)
+        if (err[k] != hipSuccess) return err[k];
+    return hipSuccess;
+}
+
+// Waits for the device and reads the window, n_out (if asked for) with it.
+lm_status read_map(lm_map* m, int64_t p0, int64_t q0, int64_t np, int64_t nq, bool mu, void* dst,
+                   uint64_t* n_out)
+{
+    HIP_TRY(hipDeviceSynchronize());
+    ReadJob r;
+    r.map = reinterpret_cast<const unsigned long long*>(m->counts);
+    r.snx = m->g.src_nx;
+    r.p0 = p0;
+    r.q0 = q0;
+    r.np = np;
+    r.n = dst ? np * nq : 0;
+    r.whole = np == m->g.src_nx && nq == m->g.src_ny;
+    r.mu = mu;
+    lm_mu_factor(m, &r.factor);
+    r.dst = static_cast<unsigned char*>(dst);
+    StageUse st(m->device);
+    if (!st) {  // no pinned memory: plain copies, converted in place
+        if (dst)
+            HIP_TRY(hipMemcpy2D(dst, (size_t)np * 8, m->counts + q0 * r.snx + p0,
+                                (size_t)r.snx * 8, (size_t)np * 8, (size_t)nq,
+                                hipMemcpyDeviceToHost));
+        for (int64_t k = 0; mu && k < r.n; ++k) {
+            uint64_t c;
+            std::memcpy(&c, r.dst + 8 * k, 8);
+            const double v = (double)c * r.factor;
+            std::memcpy(r.dst + 8 * k, &v, 8);
+        }
+        if (n_out) HIP_TRY(hipMemcpy(n_out, m->n_out.p, 8, hipMemcpyDeviceToHost));
+        return ok();
+    }
+    Lane& l = st->lane[0];
+    const int64_t small = (int64_t)(kLaneBytes / 8) - 1;
+    if (r.n <= small) {  // the window and n_out in one launch
+        LAUNCH_TRY(lm_launch_read_back(r.map, r.snx, p0, q0, np, r.whole, mu, 0, r.n, r.factor,
+                                       l.buf[0], m->n_out.as<unsigned long long>(), l.s));
+        HIP_TRY(hipStreamSynchronize(l.s));
+        if (r.n) std::memcpy(dst, l.buf[0], (size_t)r.n * 8);
+        if (n_out) *n_out = l.buf[0][r.n];
+        return ok();
+    }
+    HIP_TRY(read_job(r, *st.operator->()));
+    if (n_out) HIP_TRY(hipMemcpy(n_out, m->n_out.p, 8, hipMemcpyDeviceToHost));
+    return ok();
+}
+
+}  // namespace
+
+extern "C" {
+
 lm_status lm_read_counts(lm_map* m, uint64_t* host_counts, uint64_t* n_out, uint64_t* n_shot)
 {
     if (!m) return fail(LM_EINVAL, "map is NULL");
     lm_status st = use_device(m);
     if (st) return st;
-    HIP_TRY(hipStreamSynchronize(m->last));
-    HIP_TRY(hipDeviceSynchronize());
-    if (host_counts)
-        HIP_TRY(hipMemcpy(host_counts, m->counts, (size_t)m->g.src_nx * m->g.src_ny * 8,
-                          hipMemcpyDeviceToHost));
-    if (n_out) HIP_TRY(hipMemcpy(n_out, m->n_out.p, 8, hipMemcpyDeviceToHost));
+    st = read_map(m, 0, 0, m->g.src_nx, m->g.src_ny, false, host_counts, n_out);
+    if (st) return st;
     if (n_shot) *n_shot = m->n_shot;
     return ok();
 }
@@ -1024,15 +1279,33 @@ lm_status lm_sum_counts(lm_map* m, uint64_t* total)
     if (!m || !total) return fail(LM_EINVAL, "map or output is NULL");
     lm_status st = use_device(m);
     if (st) return st;
-    HIP_TRY(hipStreamSynchronize(m->last));
     HIP_TRY(hipDeviceSynchronize());
+    const int64_t n = (int64_t)m->g.src_nx * m->g.src_ny;
+    // eight workgroups per CU, fewer for a small map; their sums are added here
+    const int parts = (int)std::min<int64_t>(2048, ceil_div(n, 4 * LM_WG));
+    StageUse sg(m->device);
     DevBuf acc;
-    if (acc.ensure(8) != hipSuccess) return fail(LM_ENOMEM, "cannot allocate the sum");
-    LAUNCH_TRY(lm_launch_fill_u64(acc.as<unsigned long long>(), 1, 0ull, nullptr));
-    LAUNCH_TRY(lm_launch_sum_u64(reinterpret_cast<const unsigned long long*>(m->counts),
-                                 (int64_t)m->g.src_nx * m->g.src_ny, acc.as<unsigned long long>(),
-                                 nullptr));
-    HIP_TRY(hipMemcpy(total, acc.p, 8, hipMemcpyDeviceToHost));
+    std::vector<unsigned long long> host;
+    unsigned long long* out = sg ? sg->lane[0].buf[0] : nullptr;
+    hipStream_t s = sg ? sg->lane[0].s : nullptr;
+    if (!sg) {
+        if (acc.ensure((size_t)parts * 8) != hipSuccess)
+            return fail(LM_ENOMEM, "cannot allocate the sum");
+        out = acc.as<unsigned long long>();
+    }
+    LAUNCH_TRY(lm_launch_sum_u64(reinterpret_cast<const unsigned long long*>(m->counts), n, out,
+                                 parts, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    if (!sg) {
+        try {
+            host.resize(parts);
+        } catch (const std::bad_alloc&) {
+            return fail(LM_ENOMEM, "cannot allocate the sum");
+        }
+        HIP_TRY(hipMemcpy(host.data(), out, (size_t)parts * 8, hipMemcpyDeviceToHost));
+        out = host.data();
+    }
+    *total = std::accumulate(out, out + parts, 0ull);
     return ok();
 }
 
@@ -1046,17 +1319,7 @@ lm_status lm_read_counts_region(lm_map* m, int32_t p0, int32_t q0, int32_t np, i
     if (np == 0 || nq == 0) return ok();
     lm_status st = use_device(m);
     if (st) return st;
-    // packed on the device, then one contiguous copy
-    DevBuf tmp;
-    if (tmp.ensure((size_t)np * nq * 8)) return fail(LM_ENOMEM, "cannot allocate the window");
-    HIP_TRY(hipStreamSynchronize(m->last));
-    HIP_TRY(hipDeviceSynchronize());
-    LAUNCH_TRY(lm_launch_copy_region_u64(reinterpret_cast<const unsigned long long*>(m->counts),
-                                         m->g.src_nx, p0, q0, np, nq,
-                                         tmp.as<unsigned long long>(), nullptr));
-    HIP_TRY(hipStreamSynchronize(nullptr));
-    HIP_TRY(hipMemcpy(host_counts, tmp.p, (size_t)np * nq * 8, hipMemcpyDeviceToHost));
-    return ok();
+    return read_map(m, p0, q0, np, nq, false, host_counts, nullptr);
 }
 
 lm_status lm_mu_factor(const lm_map* m, double* factor)
@@ -1069,19 +1332,9 @@ lm_status lm_mu_factor(const lm_map* m, double* factor)
 lm_status lm_read_mu(lm_map* m, double* host_mu)
 {
     if (!m || !host_mu) return fail(LM_EINVAL, "NULL argument");
-    const size_t npix = (size_t)m->g.src_nx * m->g.src_ny;
-    std::vector<uint64_t> c;
-    try {
-        c.resize(npix);
-    } catch (const std::bad_alloc&) {
-        return fail(LM_ENOMEM, "cannot allocate %zu host counts", npix);
-    }
-    lm_status st = lm_read_counts(m, c.data(), nullptr, nullptr);
+    lm_status st = use_device(m);
     if (st) return st;
-    double f;
-    lm_mu_factor(m, &f);
-    for (size_t k = 0; k < npix; ++k) host_mu[k] = (double)c[k] * f;
-    return ok();
+    return read_map(m, 0, 0, m->g.src_nx, m->g.src_ny, true, host_mu, nullptr);
 }
 
 lm_status lm_reset_counts(lm_map* m, void* stream)

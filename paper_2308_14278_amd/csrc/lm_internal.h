@@ -132,10 +132,14 @@ int lm_launch_shoot_batch(const LmDesc* descs, const int64_t* offsets, const int
                           int nmaps, unsigned long long* queue, int scheme, int precision,
                           int terms, int rays_per_lane, int layout, int grid, void* stream);
 int lm_launch_fill_u64(unsigned long long* p, int64_t n, unsigned long long v, void* stream);
-int lm_launch_copy_region_u64(const unsigned long long* map, int64_t snx, int64_t p0, int64_t q0,
-                              int64_t np, int64_t nq, unsigned long long* out, void* stream);
-// *total (zeroed by the caller) += sum of p[0..n)
-int lm_launch_sum_u64(const unsigned long long* p, int64_t n, unsigned long long* total,
+// Entries [first, first + n) of a window of the map (np columns from (p0, q0);
+// whole: the map) to pinned host memory, as counts or (mu) counts x factor, and
+// *extra (may be null) after them.
+int lm_launch_read_back(const unsigned long long* map, int64_t snx, int64_t p0, int64_t q0,
+                        int64_t np, bool whole, bool mu, int64_t first, int64_t n, double factor,
+                        unsigned long long* out, const unsigned long long* extra, void* stream);
+// part[0..parts) = partial sums of p[0..n)
+int lm_launch_sum_u64(const unsigned long long* p, int64_t n, unsigned long long* part, int parts,
                       void* stream);
 // p, q: pixels (-1 outside the map); uv (may be null): continuous pixel
 // coordinates, 2 per ray, that the pixels are the floor of
