@@ -204,6 +204,8 @@ namespace {
 // pageable memory is slower per thread (10 GB/s) than the bus (57 GB/s).
 constexpr int kLanes = 8;
 constexpr size_t kLaneBytes = size_t(1) << 20;  // per buffer: 16 MiB a set
+constexpr size_t kStageBytes = 2 * kLanes * kLaneBytes;
+constexpr size_t kScratchBytes = size_t(8) << 20;  // a set's device scratch
 
 struct Lane {
     unsigned long long* buf[2] = {nullptr, nullptr};
@@ -213,7 +215,8 @@ struct Lane {
 
 struct Stage {
     int device = 0;
-    unsigned long long* mem = nullptr;
+    unsigned long long* mem = nullptr;  // the lanes' buffers, one block of kStageBytes
+    DevBuf scratch;                     // kScratchBytes of device memory
     Lane lane[kLanes];
     ~Stage()
     {
@@ -228,17 +231,26 @@ struct Stage {
     {
         device = dev;
         void* p = nullptr;
-        hipError_t e = hipHostMalloc(&p, 2 * kLanes * kLaneBytes, hipHostMallocDefault);
+        hipError_t e = hipHostMalloc(&p, kStageBytes, hipHostMallocDefault);
         if (e != hipSuccess) return e;
         mem = static_cast<unsigned long long*>(p);
-        for (int k = 0; k < kLanes; ++k) {
+        e = scratch.ensure(kScratchBytes);
+        return e != hipSuccess ? e : open(1);
+    }
+    // Makes the first n lanes ready: each stream makes a wait for the device
+    // longer, so only large reads open more than one.
+    hipError_t open(int n)
+    {
+        for (int k = 0; k < n; ++k) {
             Lane& l = lane[k];
+            if (l.s) continue;
             for (int b = 0; b < 2; ++b) {
                 l.buf[b] = mem + (2 * k + b) * (kLaneBytes / 8);
-                e = hipEventCreateWithFlags(&l.ev[b], hipEventDisableTiming);
+                if (l.ev[b]) continue;
+                const hipError_t e = hipEventCreateWithFlags(&l.ev[b], hipEventDisableTiming);
                 if (e != hipSuccess) return e;
             }
-            e = hipStreamCreateWithFlags(&l.s, hipStreamNonBlocking);
+            const hipError_t e = hipStreamCreateWithFlags(&l.s, hipStreamNonBlocking);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -598,14 +610,6 @@ lm_status prepare(lm_map* m, hipStream_t s)
     return LM_OK;
 }
 
-uint64_t splitmix64(uint64_t x)
-{
-    x += 0x9e3779b97f4a7c15ull;
-    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
-    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
-    return x ^ (x >> 31);
-}
-
 constexpr int64_t kPrecSample = 65536;   // rays probed to choose the near-sum precision
 constexpr double kPrecFp32Max = 5e-6;    // largest estimated FP32 mismatch kept in FP32
 constexpr double kPrecFp32MaxNear = 32;  // longest mean near list kept in FP32
@@ -677,54 +681,38 @@ lm_status resolve_precision(lm_map* m, hipStream_t s)
     const lm_geometry& g = m->g;
     const int64_t nrays = g.ray_nx * g.ray_ny;
     const int64_t n = std::min<int64_t>(kPrecSample, nrays);
-    std::vector<int64_t> hi(n), hj(n);
-    for (int64_t t = 0; t < n; ++t) {
-        if (n == nrays) {
-            hi[t] = t % g.ray_nx;
-            hj[t] = t / g.ray_nx;
-        } else {
-            hi[t] = (int64_t)(splitmix64(2 * (uint64_t)t) % (uint64_t)g.ray_nx);
-            hj[t] = (int64_t)(splitmix64(2 * (uint64_t)t + 1) % (uint64_t)g.ray_ny);
-        }
-    }
-    DevBuf di, dj, dp, dq, u32, uct, u64;
-    if (di.ensure(n * 8) || dj.ensure(n * 8) || dp.ensure(n * 4) || dq.ensure(n * 4) ||
-        u32.ensure(n * 16) || uct.ensure(n * 16) || u64.ensure(n * 16))
+    constexpr int kParts = 64;  // workgroups of the reduction
+    static_assert(kPrecSample * (16 + 3 * 16) + kParts * 24 <= (int64_t)kScratchBytes,
+                  "the probe fits the scratch");
+    StageUse st2(m->device);
+    DevBuf own;
+    if (!st2 && own.ensure(kScratchBytes) != hipSuccess)
         return fail(LM_ENOMEM, "cannot allocate the precision probe");
-    HIP_TRY(hipMemcpyAsync(di.p, hi.data(), n * 8, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(dj.p, hj.data(), n * 8, hipMemcpyHostToDevice, s));
+    unsigned char* dev = st2 ? st2->scratch.as<unsigned char>() : own.as<unsigned char>();
+    int64_t *di = reinterpret_cast<int64_t*>(dev), *dj = di + n;
+    double* uv[3];  // plain, centred and FP64 near sums
+    for (int k = 0; k < 3; ++k) uv[k] = reinterpret_cast<double*>(dev) + 2 * n * (k + 1);
+    double* part = reinterpret_cast<double*>(dev) + 8 * n;
+    LAUNCH_TRY(lm_launch_probe_rays(g.ray_nx, g.ray_ny, n, di, dj, s));
     const LmDesc d = make_desc(m, 0, 0, 0, 0, Exec{});
-    LAUNCH_TRY(lm_launch_trace(d, g.scheme, LM_PREC_MIXED, g.taylor_terms, di.as<int64_t>(),
-                               dj.as<int64_t>(), n, dp.as<int32_t>(), dq.as<int32_t>(),
-                               u32.as<double>(), s));
-    LAUNCH_TRY(lm_launch_trace(d, g.scheme, LM_PREC_MIXED_CENTRED, g.taylor_terms,
-                               di.as<int64_t>(), dj.as<int64_t>(), n, dp.as<int32_t>(),
-                               dq.as<int32_t>(), uct.as<double>(), s));
-    LAUNCH_TRY(lm_launch_trace(d, g.scheme, LM_PREC_MIXED_FP64, g.taylor_terms, di.as<int64_t>(),
-                               dj.as<int64_t>(), n, dp.as<int32_t>(), dq.as<int32_t>(),
-                               u64.as<double>(), s));
-    std::vector<double> a(2 * n), c(2 * n), b(2 * n);
-    HIP_TRY(hipMemcpyAsync(a.data(), u32.p, n * 16, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(c.data(), uct.p, n * 16, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(b.data(), u64.p, n * 16, hipMemcpyDeviceToHost, s));
+    const int precs[3] = {LM_PREC_MIXED, LM_PREC_MIXED_CENTRED, LM_PREC_MIXED_FP64};
+    for (int k = 0; k < 3; ++k)
+        LAUNCH_TRY(lm_launch_trace(d, g.scheme, precs[k], g.taylor_terms, di, dj, n, nullptr,
+                                   nullptr, uv[k], s));
+    LAUNCH_TRY(lm_launch_probe_moves(uv[0], uv[1], uv[2], n, g.src_nx, g.src_ny, part, kParts, s));
+    double hp[3 * kParts];
+    HIP_TRY(hipMemcpyAsync(hp, part, sizeof hp, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    double acc = 0.0, acc_c = 0.0;
-    int64_t n_in = 0;
-    auto move = [](double du, double dv) {
-        const double mv = std::fabs(du) + std::fabs(dv);
-        return std::isfinite(mv) ? std::min(1.0, mv) : 1.0;
-    };
-    for (int64_t t = 0; t < n; ++t) {
-        const double u = b[2 * t], v = b[2 * t + 1];
-        if (!(u >= 0.0 && u < g.src_nx && v >= 0.0 && v < g.src_ny)) continue;
-        ++n_in;
-        acc += move(a[2 * t] - u, a[2 * t + 1] - v);
-        acc_c += move(c[2 * t] - u, c[2 * t + 1] - v);
+    double acc = 0.0, acc_c = 0.0, n_in = 0.0;
+    for (int k = 0; k < kParts; ++k) {
+        acc += hp[3 * k];
+        acc_c += hp[3 * k + 1];
+        n_in += hp[3 * k + 2];
     }
     // per ray imaged into the map: a shot region that lands inside the map
     // sees this rate, however few of the lattice's rays reach the map
-    m->prec_est = n_in > 0 ? acc / (double)n_in : 0.0;
-    m->prec_est_centred = n_in > 0 ? acc_c / (double)n_in : 0.0;
+    m->prec_est = n_in > 0 ? acc / n_in : 0.0;
+    m->prec_est_centred = n_in > 0 ? acc_c / n_in : 0.0;
     const bool short_lists = mean_near(m) <= kPrecFp32MaxNear;
     if (short_lists && m->prec_est <= kPrecFp32Max)
         m->prec = LM_PREC_MIXED;
@@ -1041,39 +1029,49 @@ lm_status lm_set_lenses(lm_map* m, const double* x, const double* y, const doubl
         std::vector<int64_t> pos(hist.begin(), hist.end());
         for (int64_t k = 0; k < n; ++k) order[pos[key[k]]++] = k;  // stable counting sort
     }
-    std::vector<double> sx(n), sy(n), sm(n);
-    std::vector<float> fx(n), fy(n), fm(n);
-    std::vector<int32_t> sI(n), sJ(n);
-    for (int64_t t = 0; t < n; ++t) {
-        const int64_t k = order[t];
-        sx[t] = x[k];
-        sy[t] = y[k];
-        sm[t] = mass[k];
-        fx[t] = (float)x[k];
-        fy[t] = (float)y[k];
-        fm[t] = (float)mass[k];
-        sI[t] = I[k];
-        sJ[t] = J[k];
-    }
-    const size_t nn = (size_t)std::max<int64_t>(n, 1);
+    const size_t nn = (size_t)std::max<int64_t>(n, 1), ns = start.size();
     if (m->lx.ensure(nn * 8) || m->ly.ensure(nn * 8) || m->lmd.ensure(nn * 8) ||
         m->lxf.ensure(nn * 4) || m->lyf.ensure(nn * 4) || m->lmf.ensure(nn * 4) ||
         m->lI.ensure(nn * 4) || m->lJ.ensure(nn * 4))
         return fail(LM_ENOMEM, "cannot allocate lens arrays");
-    if (n > 0) {
-        HIP_TRY(hipMemcpy(m->lx.p, sx.data(), n * 8, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(m->ly.p, sy.data(), n * 8, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(m->lmd.p, sm.data(), n * 8, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(m->lxf.p, fx.data(), n * 4, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(m->lyf.p, fy.data(), n * 4, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(m->lmf.p, fm.data(), n * 4, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(m->lI.p, sI.data(), n * 4, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(m->lJ.p, sJ.data(), n * 4, hipMemcpyHostToDevice));
-    }
-    if (g.scheme == LM_SCHEME_INTERP) {
-        if (m->cell_start.ensure(start.size() * 4))
-            return fail(LM_ENOMEM, "cannot allocate the level-1 index");
-        HIP_TRY(hipMemcpy(m->cell_start.p, start.data(), start.size() * 4, hipMemcpyHostToDevice));
+    if (m->cell_start.ensure(ns * 4)) return fail(LM_ENOMEM, "cannot allocate the level-1 index");
+    // one block for the upload: sorted x, y, m, level-1 cells, CSR
+    const size_t bytes = 32 * (size_t)n + 4 * ns;
+    if (bytes > 0) {
+        StageUse sg(m->device);
+        const bool pinned = sg && bytes <= kStageBytes;
+        std::vector<double> block;
+        DevBuf dblock;
+        double* w = pinned ? reinterpret_cast<double*>(sg->mem) : nullptr;
+        if (!pinned) {
+            try {
+                block.resize((bytes + 7) / 8);
+            } catch (const std::bad_alloc&) {
+                return fail(LM_ENOMEM, "cannot allocate %zu bytes for the lenses", bytes);
+            }
+            if (dblock.ensure(bytes)) return fail(LM_ENOMEM, "cannot allocate lens arrays");
+            w = block.data();
+        }
+        int32_t* wc = reinterpret_cast<int32_t*>(w + 3 * n);
+        for (int64_t t = 0; t < n; ++t) {
+            const int64_t k = order[t];
+            w[t] = x[k];
+            w[n + t] = y[k];
+            w[2 * n + t] = mass[k];
+            wc[t] = I[k];
+            wc[n + t] = J[k];
+        }
+        std::copy(start.begin(), start.end(), wc + 2 * n);
+        const double* src = w;
+        if (!pinned) {
+            HIP_TRY(hipMemcpy(dblock.p, w, bytes, hipMemcpyHostToDevice));
+            src = dblock.as<double>();
+        }
+        const LmLensArrays o{m->lx.as<double>(),  m->ly.as<double>(),  m->lmd.as<double>(),
+                             m->lxf.as<float>(),  m->lyf.as<float>(),  m->lmf.as<float>(),
+                             m->lI.as<int32_t>(), m->lJ.as<int32_t>(), m->cell_start.as<int32_t>()};
+        LAUNCH_TRY(lm_launch_lens_upload(src, n, (int64_t)ns, o, nullptr));
+        HIP_TRY(hipStreamSynchronize(nullptr));
     }
     m->h_start.swap(start);
     m->nlens = n;
@@ -1191,6 +1189,8 @@ hipError_t read_job(const ReadJob& r, Stage& st)
     const int64_t nk = ceil_div(r.n, (int64_t)(kLaneBytes / 8));
     const int nt = (int)std::min<int64_t>(kLanes, nk / 2);
     if (nt < 2) return read_lane(r, st.lane[0], 0, 1);
+    const hipError_t opened = st.open(nt);
+    if (opened != hipSuccess) return opened;
     hipError_t err[kLanes];
     std::thread th[kLanes];
     int started = 1;  // lane 0 runs here
@@ -1366,7 +1366,6 @@ lm_status lm_read_coeffs(lm_map* m, int64_t ci, int64_t cj, double* a)
         st = prepare(m, nullptr);
         if (st) return st;
     }
-    if (m->last) HIP_TRY(hipStreamSynchronize(m->last));
     HIP_TRY(hipDeviceSynchronize());
     LmCoef c;
     HIP_TRY(hipMemcpy(&c, m->coef.as<LmCoef>() + (cj * m->ncx + ci), sizeof c,
@@ -1516,7 +1515,6 @@ lm_status lm_find_peaks(lm_map* m, const int32_t* tracks, int32_t n_tracks, int3
     DevBuf dt, df;
     const size_t nf = (size_t)n_tracks * m->g.src_nx;
     if (dt.ensure((size_t)n_tracks * 4) || df.ensure(nf)) return fail(LM_ENOMEM, "cannot allocate");
-    HIP_TRY(hipStreamSynchronize(m->last));
     HIP_TRY(hipDeviceSynchronize());
     HIP_TRY(hipMemcpy(dt.p, tracks, (size_t)n_tracks * 4, hipMemcpyHostToDevice));
     LAUNCH_TRY(lm_launch_peaks(reinterpret_cast<const unsigned long long*>(m->counts), m->g.src_nx,
@@ -1583,7 +1581,6 @@ lm_status peak_stats_run(lm_map* m, const int32_t* tracks, int32_t n_tracks, int
     if (n_tracks == 0) return ok();
     lm_status st = use_device(m);
     if (st) return st;
-    HIP_TRY(hipStreamSynchronize(m->last));
     HIP_TRY(hipDeviceSynchronize());
     HIP_TRY(hipMemcpy(d.tracks, tracks, (size_t)n_tracks * 4, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(d.edges, beta_edges, (size_t)(n_bins + 1) * 8, hipMemcpyHostToDevice));

@@ -1588,10 +1588,15 @@ __global__ __launch_bounds__(kWG) void k_trace(LmDesc d, const int64_t* __restri
     const int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x;
     if (t >= n) return;
     double* u = uv ? uv + 2 * t : nullptr;
+    int32_t p, q;
     if (d.fold)
-        trace_one<SCHEME, PREC, P, true>(d, ii[t], jj[t], po[t], qo[t], u);
+        trace_one<SCHEME, PREC, P, true>(d, ii[t], jj[t], p, q, u);
     else
-        trace_one<SCHEME, PREC, P, false>(d, ii[t], jj[t], po[t], qo[t], u);
+        trace_one<SCHEME, PREC, P, false>(d, ii[t], jj[t], p, q, u);
+    if (po) {
+        po[t] = p;
+        qo[t] = q;
+    }
 }
 
 // Deflection at an arbitrary position, rebased on the level-2 cell holding it.

@@ -112,7 +112,23 @@ struct LmDesc {
     unsigned long long* n_out;
 };
 
+// Device lens arrays of a map (LmDesc's, writable).
+struct LmLensArrays {
+    double *lx, *ly, *lmd;
+    float *lxf, *lyf, *lmf;
+    int32_t *lI, *lJ, *cell_start;
+};
+
 // Launchers implemented in lm_kernels.hip (return hipError_t as int).
+// Lens arrays from a pinned block: n x, y, m (doubles), n I and J, nstart CSR entries.
+int lm_launch_lens_upload(const double* src, int64_t n, int64_t nstart, const LmLensArrays& o,
+                          void* stream);
+// The precision probe: n lattice rays (every ray when n is the lattice's number), and
+// part[3 k] .. = sums of the moves of a and c against b and the rays in the map, per workgroup.
+int lm_launch_probe_rays(int64_t nx, int64_t ny, int64_t n, int64_t* ii, int64_t* jj,
+                         void* stream);
+int lm_launch_probe_moves(const double* a, const double* c, const double* b, int64_t n, int snx,
+                          int sny, double* part, int parts, void* stream);
 // The rectangle sheet's holomorphic part added to every level-2 cell's
 // coefficients (after the far-field kernels).
 int lm_launch_sheet(const LmDesc& d, int terms, LmCoef* coef, void* stream);
@@ -141,7 +157,7 @@ int lm_launch_read_back(const unsigned long long* map, int64_t snx, int64_t p0, 
 // part[0..parts) = partial sums of p[0..n)
 int lm_launch_sum_u64(const unsigned long long* p, int64_t n, unsigned long long* part, int parts,
                       void* stream);
-// p, q: pixels (-1 outside the map); uv (may be null): continuous pixel
+// p, q: pixels (-1 outside the map; may be null); uv (may be null): continuous pixel
 // coordinates, 2 per ray, that the pixels are the floor of
 int lm_launch_trace(const LmDesc& d, int scheme, int precision, int terms, const int64_t* ii,
                     const int64_t* jj, int64_t n, int32_t* p, int32_t* q, double* uv,

@@ -322,6 +322,88 @@ __global__ __launch_bounds__(kWG) void k_read_back(const unsigned long long* __r
     if (t == 0 && extra) out[n] = *extra;
 }
 
+// --------------------------------------------- a new lens field
+
+// The lens arrays from one pinned block (n x, y, m as doubles, then n I and J,
+// then nstart CSR entries): every array, the FP32 copies among them, in one
+// launch, where nine copies from pageable memory took most of the call
+// (latency: ~12 us each).
+__global__ __launch_bounds__(kWG) void k_lens_upload(const double* __restrict__ src, int64_t n,
+                                                     int64_t nstart, LmLensArrays o)
+{
+    const int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x;
+    const int32_t* cells = (const int32_t*)(src + 3 * n);
+    if (t < n) {
+        const double x = src[t], y = src[n + t], m = src[2 * n + t];
+        o.lx[t] = x;
+        o.ly[t] = y;
+        o.lmd[t] = m;
+        o.lxf[t] = (float)x;
+        o.lyf[t] = (float)y;
+        o.lmf[t] = (float)m;
+        o.lI[t] = cells[t];
+        o.lJ[t] = cells[n + t];
+    }
+    if (t < nstart) o.cell_start[t] = cells[2 * n + t];
+}
+
+__device__ __forceinline__ uint64_t splitmix64(uint64_t x)
+{
+    x += 0x9e3779b97f4a7c15ull;
+    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+    return x ^ (x >> 31);
+}
+
+// The precision probe's rays: all n of a lattice of n rays, else n at fixed
+// counter-based positions.
+__global__ __launch_bounds__(kWG) void k_probe_rays(int64_t nx, int64_t ny, int64_t n, bool all,
+                                                    int64_t* __restrict__ ii,
+                                                    int64_t* __restrict__ jj)
+{
+    const int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x;
+    if (t >= n) return;
+    ii[t] = all ? t % nx : (int64_t)(splitmix64(2 * (uint64_t)t) % (uint64_t)nx);
+    jj[t] = all ? t / nx : (int64_t)(splitmix64(2 * (uint64_t)t + 1) % (uint64_t)ny);
+}
+
+// How far plain (a) and centred (c) FP32 near sums move the images of the
+// probe's rays from those with FP64 near sums (b): per workgroup the sums of
+// |du| + |dv| (at most 1 a ray, 1 for a non-finite one) over the rays whose
+// images lie in the map, and their number.
+__global__ __launch_bounds__(kWG) void k_probe_moves(const double2* __restrict__ a,
+                                                     const double2* __restrict__ c,
+                                                     const double2* __restrict__ b, int64_t n,
+                                                     double snx, double sny,
+                                                     double* __restrict__ part)
+{
+    __shared__ double ws[3][LM_WAVES];
+    double s[3] = {0.0, 0.0, 0.0};
+    auto move = [](double du, double dv) {
+        const double mv = fabs(du) + fabs(dv);
+        return mv < 1.0 ? mv : 1.0;
+    };
+    for (int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x; t < n;
+         t += (int64_t)gridDim.x * kWG) {
+        const double2 v = b[t];
+        if (!(v.x >= 0.0 && v.x < snx && v.y >= 0.0 && v.y < sny)) continue;
+        const double2 p = a[t], q = c[t];
+        s[0] += move(p.x - v.x, p.y - v.y);
+        s[1] += move(q.x - v.x, q.y - v.y);
+        s[2] += 1.0;
+    }
+    for (int k = 0; k < 3; ++k) {
+        for (int o = 32; o > 0; o >>= 1) s[k] += __shfl_xor(s[k], o, 64);
+        if ((threadIdx.x & 63) == 0) ws[k][threadIdx.x >> 6] = s[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double v = 0.0;
+        for (int w = 0; w < LM_WAVES; ++w) v += ws[threadIdx.x][w];
+        part[3 * blockIdx.x + threadIdx.x] = v;
+    }
+}
+
 // ------------------------------------------------ the rectangle sheet
 
 struct Cd {
@@ -625,6 +707,34 @@ int lm_launch_read_back(const unsigned long long* map, int64_t snx, int64_t p0, 
     else
         X(false, false);
 #undef X
+    return (int)hipGetLastError();
+}
+
+int lm_launch_lens_upload(const double* src, int64_t n, int64_t nstart, const LmLensArrays& o,
+                          void* stream)
+{
+    const int64_t m = n > nstart ? n : nstart;
+    if (m <= 0) return 0;
+    hipLaunchKernelGGL(k_lens_upload, dim3((unsigned)((m + kWG - 1) / kWG)), dim3(kWG), 0,
+                       (hipStream_t)stream, src, n, nstart, o);
+    return (int)hipGetLastError();
+}
+
+int lm_launch_probe_rays(int64_t nx, int64_t ny, int64_t n, int64_t* ii, int64_t* jj,
+                         void* stream)
+{
+    if (n <= 0) return 0;
+    hipLaunchKernelGGL(k_probe_rays, dim3((unsigned)((n + kWG - 1) / kWG)), dim3(kWG), 0,
+                       (hipStream_t)stream, nx, ny, n, n == nx * ny, ii, jj);
+    return (int)hipGetLastError();
+}
+
+int lm_launch_probe_moves(const double* a, const double* c, const double* b, int64_t n, int snx,
+                          int sny, double* part, int parts, void* stream)
+{
+    hipLaunchKernelGGL(k_probe_moves, dim3((unsigned)parts), dim3(kWG), 0, (hipStream_t)stream,
+                       (const double2*)a, (const double2*)c, (const double2*)b, n, (double)snx,
+                       (double)sny, part);
     return (int)hipGetLastError();
 }
 
