@@ -363,8 +363,8 @@ lm_status lm_peak_stats(lm_map* m, const int32_t* tracks, int32_t n_tracks, int3
 /* lm_peak_stats without any device allocation, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same arguments, results and errors as
- * lm_peak_stats; its device staging (the rows, the bin of every pixel column,
- * the bin edges and the two histograms, 4.2 MB) lives in a scratch array that
+ * lm_peak_stats; its device staging (the rows, the first pixel column of every
+ * bin and the two histograms, 0.2 MB) lives in a scratch array that
  * the library holds on each device it runs on until the process ends, which
  * limits a call to at most 8192 rows, maps of at most 2^20 columns and at most
  * 4096 bins (LM_EINVAL beyond).  Every call on one device shares that array,

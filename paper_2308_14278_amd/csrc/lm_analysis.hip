@@ -7,9 +7,14 @@
 // (3 N_ij - S)^2 > 3 k^2 S, decided exactly in integers.  True peak: a
 // candidate with a candidate among (i-1, j-1..j+1) and among (i+1, j-1..j+1).
 //
-// k_peak_bins gathers the statistics of Sec. 4.2 (Figs. 4 and 5): the true
-// peaks of the listed light curves per bin of distance to the caustic (bin of
-// pixel j given by the host) and the sum of their counts, both exact integers.
+// k_peak_stats gathers the statistics of Sec. 4.2 (Figs. 4 and 5): the true
+// peaks of the listed light curves per bin of distance to the caustic and the
+// sum of their counts, both exact integers.
+//
+// Both kernels are latency-bound (ten curves of a 3694-pixel map read 0.9 MB):
+// what a call costs is its copies, launches and waits.  Each call is one launch
+// that takes short lists by value and writes its results to the caller's
+// (pinned) memory.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -21,7 +26,7 @@
 namespace {
 
 // Scratch memory of the allocation-free peak statistics: the listed rows, the
-// bin of every pixel column and the two histograms, at fixed offsets.  Each
+// first pixel column of every bin and the two histograms, at fixed offsets.  Each
 // device holds its own copy; host code reaches it only through the address
 // hipGetSymbolAddress returns on that device.
 static __device__ __align__(256) unsigned char scratch[LM_SCRATCH_BYTES];
@@ -46,31 +51,6 @@ __device__ __forceinline__ bool candidate(const unsigned long long* __restrict__
     return (unsigned __int128)tl * tl > (unsigned __int128)k2x3 * s;
 }
 
-__global__ __launch_bounds__(256) void k_peaks(const unsigned long long* __restrict__ counts,
-                                               int64_t nx, int64_t ny,
-                                               const int32_t* __restrict__ tracks, int64_t nt,
-                                               unsigned k2x3, uint8_t* __restrict__ flags)
-{
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= nt * nx) return;
-    const int64_t t = idx / nx, j = idx - t * nx;
-    const int64_t i = tracks[t];
-    uint8_t f = 0;
-    if (candidate(counts, nx, i, j, k2x3)) {
-        f = 1;
-        if (i > 0 && i < ny - 1) {
-            const bool left = candidate(counts, nx, i - 1, j - 1, k2x3) ||
-                              candidate(counts, nx, i - 1, j, k2x3) ||
-                              candidate(counts, nx, i - 1, j + 1, k2x3);
-            const bool right = candidate(counts, nx, i + 1, j - 1, k2x3) ||
-                               candidate(counts, nx, i + 1, j, k2x3) ||
-                               candidate(counts, nx, i + 1, j + 1, k2x3);
-            if (left && right) f |= 2;
-        }
-    }
-    flags[idx] = f;
-}
-
 __device__ __forceinline__ bool true_peak(const unsigned long long* __restrict__ c, int64_t nx,
                                           int64_t ny, int64_t i, int64_t j, unsigned k2x3)
 {
@@ -81,82 +61,89 @@ __device__ __forceinline__ bool true_peak(const unsigned long long* __restrict__
                     candidate(c, nx, i + 1, j + 1, k2x3));
 }
 
-// Distance bin of every pixel column: the bin holding the column centre
-// x0 + (p + 1/2) dx, with the multiply and the add rounded separately as the
-// host computes the same centres.
-__global__ __launch_bounds__(256) void k_column_bins(double x0, double dx, int64_t nx,
-                                                     const double* __restrict__ edges, int nb,
-                                                     int32_t* __restrict__ bin_of)
+// Flags of pixels j of the listed rows: one light curve per grid row (more than
+// 65535 in turns), the rows from `tracks` or, if null, from the argument.
+__global__ __launch_bounds__(256) void k_peaks(const unsigned long long* __restrict__ counts,
+                                               int64_t nx, int64_t ny, LmTracks rows,
+                                               const int32_t* __restrict__ tracks, int64_t nt,
+                                               unsigned k2x3, uint8_t* __restrict__ flags)
 {
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= nx) return;
-    const double c = __dadd_rn(x0, __dmul_rn((double)p + 0.5, dx));
-    int b = -1;
-    if (c >= edges[0] && c < edges[nb]) {
-        int lo = 0, hi = nb - 1;  // the largest b with edges[b] <= c
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (edges[mid] <= c)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        b = lo;
+    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (j >= nx) return;
+    for (int64_t t = blockIdx.y; t < nt; t += gridDim.y) {
+        const int64_t i = tracks ? tracks[t] : rows.row[t];
+        uint8_t f = 0;
+        if (candidate(counts, nx, i, j, k2x3)) f = true_peak(counts, nx, ny, i, j, k2x3) ? 3 : 1;
+        flags[t * nx + j] = f;
     }
-    bin_of[p] = b;
 }
 
-// One thread per (light curve t, pixel j); true peaks are rare, so their bins
-// are added to with global atomics.
-__global__ __launch_bounds__(256) void k_peak_bins(const unsigned long long* __restrict__ counts,
-                                                   int64_t nx, int64_t ny,
-                                                   const int32_t* __restrict__ tracks, int64_t nt,
-                                                   unsigned k2x3, const int32_t* __restrict__ bin_of,
-                                                   unsigned long long* __restrict__ peaks,
-                                                   unsigned long long* __restrict__ heights)
+// Statistics of the listed rows over the pixel columns [col[0], col[nb]); column
+// p belongs to the last bin b with col[b] <= p.  True peaks are rare, so they
+// search their bin and add to hist (peaks[nb], heights[nb]) with global atomics.
+// The last workgroup to finish moves the sums to out, leaving hist and *done
+// zero as it found them.
+__global__ __launch_bounds__(256) void k_peak_stats(const unsigned long long* __restrict__ counts,
+                                                    int64_t nx, int64_t ny, LmTracks rows,
+                                                    const int32_t* __restrict__ tracks, int64_t nt,
+                                                    unsigned k2x3, LmBins bins,
+                                                    const int32_t* __restrict__ cols, int c0, int c1,
+                                                    int nb, unsigned long long* hist,
+                                                    unsigned* done, unsigned long long* out)
 {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= nt * nx) return;
-    const int64_t t = idx / nx, j = idx - t * nx;
-    const int b = bin_of[j];
-    if (b < 0) return;
-    const int64_t i = tracks[t];
-    if (!true_peak(counts, nx, ny, i, j, k2x3)) return;
-    atomicAdd(&peaks[b], 1ull);
-    atomicAdd(&heights[b], counts[i * nx + j]);
+    __shared__ bool last;
+    const int64_t j = c0 + (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (j < c1) {
+        for (int64_t t = blockIdx.y; t < nt; t += gridDim.y) {
+            const int64_t i = tracks ? tracks[t] : rows.row[t];
+            if (!true_peak(counts, nx, ny, i, j, k2x3)) continue;
+            int lo = 0, hi = nb - 1;  // the last b with col[b] <= j (col[0] <= j < col[nb])
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if ((cols ? cols[mid] : bins.col[mid]) <= j)
+                    lo = mid;
+                else
+                    hi = mid - 1;
+            }
+            atomicAdd(&hist[lo], 1ull);
+            atomicAdd(&hist[nb + lo], counts[i * nx + j]);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = atomicAdd(done, 1u) == gridDim.x * gridDim.y - 1u;
+    }
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    for (int b = threadIdx.x; b < 2 * nb; b += 256) out[b] = atomicExch(&hist[b], 0ull);
+    if (threadIdx.x == 0) atomicExch(done, 0u);
 }
 
 }  // namespace
 
-int lm_launch_column_bins(double x0, double dx, int64_t nx, const double* edges, int nb,
-                          int32_t* bin_of, void* stream)
+int lm_launch_peak_stats(const unsigned long long* counts, int64_t nx, int64_t ny,
+                         const LmTracks& rows, const int32_t* tracks, int64_t nt, int k,
+                         const LmBins& bins, const int32_t* cols, int c0, int c1, int nb,
+                         unsigned long long* hist, unsigned* done, unsigned long long* out,
+                         void* stream)
 {
-    if (nx <= 0) return 0;
-    hipLaunchKernelGGL(k_column_bins, dim3((unsigned)((nx + 255) / 256)), dim3(256), 0,
-                       (hipStream_t)stream, x0, dx, nx, edges, nb, bin_of);
+    if (nt <= 0) return 0;
+    const int64_t w = c1 > c0 ? c1 - c0 : 1;
+    const dim3 grid((unsigned)((w + 255) / 256), (unsigned)(nt < 65535 ? nt : 65535));
+    hipLaunchKernelGGL(k_peak_stats, grid, dim3(256), 0, (hipStream_t)stream, counts, nx, ny, rows,
+                       tracks, nt, (unsigned)(3 * k * k), bins, cols, c0, c1, nb, hist, done, out);
     return (int)hipGetLastError();
 }
 
-int lm_launch_peak_bins(const unsigned long long* counts, int64_t nx, int64_t ny,
-                        const int32_t* tracks, int64_t nt, int k, const int32_t* bin_of,
-                        unsigned long long* peaks, unsigned long long* heights, void* stream)
-{
-    const int64_t n = nt * nx;
-    if (n <= 0) return 0;
-    hipLaunchKernelGGL(k_peak_bins, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       (hipStream_t)stream, counts, nx, ny, tracks, nt, (unsigned)(3 * k * k),
-                       bin_of, peaks, heights);
-    return (int)hipGetLastError();
-}
-
-int lm_launch_peaks(const unsigned long long* counts, int64_t nx, int64_t ny,
+int lm_launch_peaks(const unsigned long long* counts, int64_t nx, int64_t ny, const LmTracks& rows,
                     const int32_t* tracks, int64_t nt, int k, uint8_t* flags, void* stream)
 {
-    const int64_t n = nt * nx;
-    if (n <= 0) return 0;
-    hipLaunchKernelGGL(k_peaks, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       (hipStream_t)stream, counts, nx, ny, tracks, nt, (unsigned)(3 * k * k),
-                       flags);
+    if (nt <= 0 || nx <= 0) return 0;
+    const dim3 grid((unsigned)((nx + 255) / 256), (unsigned)(nt < 65535 ? nt : 65535));
+    hipLaunchKernelGGL(k_peaks, grid, dim3(256), 0, (hipStream_t)stream, counts, nx, ny, rows,
+                       tracks, nt, (unsigned)(3 * k * k), flags);
     return (int)hipGetLastError();
 }
 

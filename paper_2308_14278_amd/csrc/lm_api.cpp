@@ -206,6 +206,11 @@ constexpr int kLanes = 8;
 constexpr size_t kLaneBytes = size_t(1) << 20;  // per buffer: 16 MiB a set
 constexpr size_t kStageBytes = 2 * kLanes * kLaneBytes;
 constexpr size_t kScratchBytes = size_t(8) << 20;  // a set's device scratch
+// ... of which the upper part holds histograms and a counter, zero between calls
+constexpr int kHistBins = 1 << 16;
+constexpr size_t kHistOff = size_t(6) << 20;
+constexpr size_t kDoneOff = kHistOff + 16 * (size_t)kHistBins;
+static_assert(kDoneOff + 8 <= kScratchBytes, "histograms fit the scratch");
 
 struct Lane {
     unsigned long long* buf[2] = {nullptr, nullptr};
@@ -235,7 +240,16 @@ struct Stage {
         if (e != hipSuccess) return e;
         mem = static_cast<unsigned long long*>(p);
         e = scratch.ensure(kScratchBytes);
-        return e != hipSuccess ? e : open(1);
+        if (e == hipSuccess) e = open(1);
+        return e != hipSuccess ? e : clear_hist();
+    }
+    unsigned char* dev() const { return scratch.as<unsigned char>(); }
+    hipError_t clear_hist()
+    {
+        const hipError_t e = (hipError_t)lm_launch_fill_u64(
+            reinterpret_cast<unsigned long long*>(dev() + kHistOff), 2 * (int64_t)kHistBins + 1,
+            0ull, lane[0].s);
+        return e != hipSuccess ? e : hipStreamSynchronize(lane[0].s);
     }
     // Makes the first n lanes ready: each stream makes a wait for the device
     // longer, so only large reads open more than one.
@@ -682,11 +696,11 @@ lm_status resolve_precision(lm_map* m, hipStream_t s)
     const int64_t nrays = g.ray_nx * g.ray_ny;
     const int64_t n = std::min<int64_t>(kPrecSample, nrays);
     constexpr int kParts = 64;  // workgroups of the reduction
-    static_assert(kPrecSample * (16 + 3 * 16) + kParts * 24 <= (int64_t)kScratchBytes,
+    static_assert(kPrecSample * (16 + 3 * 16) + kParts * 24 <= (int64_t)kHistOff,
                   "the probe fits the scratch");
     StageUse st2(m->device);
     DevBuf own;
-    if (!st2 && own.ensure(kScratchBytes) != hipSuccess)
+    if (!st2 && own.ensure(kHistOff) != hipSuccess)
         return fail(LM_ENOMEM, "cannot allocate the precision probe");
     unsigned char* dev = st2 ? st2->scratch.as<unsigned char>() : own.as<unsigned char>();
     int64_t *di = reinterpret_cast<int64_t*>(dev), *dj = di + n;
@@ -698,7 +712,7 @@ lm_status resolve_precision(lm_map* m, hipStream_t s)
     const int precs[3] = {LM_PREC_MIXED, LM_PREC_MIXED_CENTRED, LM_PREC_MIXED_FP64};
     for (int k = 0; k < 3; ++k)
         LAUNCH_TRY(lm_launch_trace(d, g.scheme, precs[k], g.taylor_terms, di, dj, n, nullptr,
-                                   nullptr, uv[k], s));
+                                   nullptr, uv[k], LmUnits{}, s));
     LAUNCH_TRY(lm_launch_probe_moves(uv[0], uv[1], uv[2], n, g.src_nx, g.src_ny, part, kParts, s));
     double hp[3 * kParts];
     HIP_TRY(hipMemcpyAsync(hp, part, sizeof hp, hipMemcpyDeviceToHost, s));
@@ -1441,27 +1455,47 @@ lm_status trace_rays(lm_map* m, const int64_t* i, const int64_t* j, int64_t n, i
     }
     st = resolve_precision(m, nullptr);
     if (st) return st;
-    DevBuf di, dj, dp, dq, duv;
-    if (di.ensure((size_t)n * 8) || dj.ensure((size_t)n * 8) || dp.ensure((size_t)n * 4) ||
-        dq.ensure((size_t)n * 4) || (beta && duv.ensure((size_t)n * 16)))
-        return fail(LM_ENOMEM, "cannot allocate probe buffers");
+    // ray indices and results in pinned memory, read and written by the kernel;
+    // kStageBytes of them at a time
+    StageUse sg(m->device);
+    std::vector<unsigned char> host;
+    DevBuf dev;
+    const size_t per = 16 + (beta ? 16 : 8);  // bytes per ray
+    const int64_t chunk = std::min<int64_t>(n, (int64_t)(kStageBytes / per));
+    if (!sg) {
+        try {
+            host.resize((size_t)chunk * per);
+        } catch (const std::bad_alloc&) {
+            return fail(LM_ENOMEM, "cannot allocate probe buffers");
+        }
+        if (dev.ensure((size_t)chunk * per)) return fail(LM_ENOMEM, "cannot allocate probe buffers");
+    }
+    unsigned char* h = sg ? reinterpret_cast<unsigned char*>(sg->mem) : host.data();
+    unsigned char* k = sg ? h : dev.as<unsigned char>();  // as the kernel sees them
     HIP_TRY(hipStreamSynchronize(m->last));
-    HIP_TRY(hipMemcpy(di.p, i, (size_t)n * 8, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(dj.p, j, (size_t)n * 8, hipMemcpyHostToDevice));
-    LmDesc d = make_desc(m, 0, 0, 0, 0, Exec{});
-    LAUNCH_TRY(lm_launch_trace(d, m->g.scheme, m->prec, m->g.taylor_terms, di.as<int64_t>(),
-                               dj.as<int64_t>(), n, dp.as<int32_t>(), dq.as<int32_t>(),
-                               beta ? duv.as<double>() : nullptr, nullptr));
-    HIP_TRY(hipStreamSynchronize(nullptr));
-    if (p) HIP_TRY(hipMemcpy(p, dp.p, (size_t)n * 4, hipMemcpyDeviceToHost));
-    if (q) HIP_TRY(hipMemcpy(q, dq.p, (size_t)n * 4, hipMemcpyDeviceToHost));
-    if (beta) {
-        HIP_TRY(hipMemcpy(beta, duv.p, (size_t)n * 16, hipMemcpyDeviceToHost));
-        // pixel coordinates -> source-plane position (pixel (p, q) starts at
-        // src_x0 + p src_dx, src_y0 + q src_dy)
-        for (int64_t t = 0; t < n; ++t) {
-            beta[2 * t] = m->g.src_x0 + beta[2 * t] * m->g.src_dx;
-            beta[2 * t + 1] = m->g.src_y0 + beta[2 * t + 1] * m->g.src_dy;
+    const LmDesc d = make_desc(m, 0, 0, 0, 0, Exec{});
+    const LmUnits units{m->g.src_x0, m->g.src_y0, m->g.src_dx, m->g.src_dy, beta != nullptr};
+    for (int64_t t0 = 0; t0 < n; t0 += chunk) {
+        const int64_t c = std::min(chunk, n - t0);
+        std::memcpy(h, i + t0, (size_t)c * 8);
+        std::memcpy(h + 8 * c, j + t0, (size_t)c * 8);
+        if (!sg) HIP_TRY(hipMemcpy(k, h, (size_t)c * 16, hipMemcpyHostToDevice));
+        const int64_t* ki = reinterpret_cast<const int64_t*>(k);
+        int32_t* kp = beta ? nullptr : reinterpret_cast<int32_t*>(k + 16 * c);
+        LAUNCH_TRY(lm_launch_trace(d, m->g.scheme, m->prec, m->g.taylor_terms, ki, ki + c, c, kp,
+                                   beta ? nullptr : kp + c,
+                                   beta ? reinterpret_cast<double*>(k + 16 * c) : nullptr, units,
+                                   nullptr));
+        HIP_TRY(hipStreamSynchronize(nullptr));
+        if (!sg)
+            HIP_TRY(hipMemcpy(h + 16 * c, k + 16 * c, (size_t)c * (per - 16),
+                              hipMemcpyDeviceToHost));
+        const unsigned char* r = h + 16 * c;
+        if (beta) {
+            std::memcpy(beta + 2 * t0, r, (size_t)c * 16);
+        } else {
+            if (p) std::memcpy(p + t0, r, (size_t)c * 4);
+            if (q) std::memcpy(q + t0, r + 4 * c, (size_t)c * 4);
         }
     }
     return ok();
@@ -1512,16 +1546,39 @@ lm_status lm_find_peaks(lm_map* m, const int32_t* tracks, int32_t n_tracks, int3
         return fail(LM_EUNSUPPORTED, "too many track pixels");
     lm_status st = use_device(m);
     if (st) return st;
-    DevBuf dt, df;
-    const size_t nf = (size_t)n_tracks * m->g.src_nx;
-    if (dt.ensure((size_t)n_tracks * 4) || df.ensure(nf)) return fail(LM_ENOMEM, "cannot allocate");
     HIP_TRY(hipDeviceSynchronize());
-    HIP_TRY(hipMemcpy(dt.p, tracks, (size_t)n_tracks * 4, hipMemcpyHostToDevice));
-    LAUNCH_TRY(lm_launch_peaks(reinterpret_cast<const unsigned long long*>(m->counts), m->g.src_nx,
-                               m->g.src_ny, dt.as<int32_t>(), n_tracks, k, df.as<uint8_t>(),
-                               nullptr));
-    HIP_TRY(hipStreamSynchronize(nullptr));
-    HIP_TRY(hipMemcpy(flags, df.p, nf, hipMemcpyDeviceToHost));
+    const int64_t nx = m->g.src_nx;
+    const unsigned long long* counts = reinterpret_cast<const unsigned long long*>(m->counts);
+    LmTracks rows{};
+    StageUse sg(m->device);
+    DevBuf dt, df;
+    // as many light curves at a time as pinned memory takes flags of (all of
+    // them into device memory where it takes none)
+    const bool pinned = sg && nx <= (int64_t)kStageBytes;
+    const int64_t per =
+        pinned ? std::min<int64_t>(n_tracks, (int64_t)kStageBytes / nx) : (int64_t)n_tracks;
+    if (!pinned && df.ensure((size_t)per * nx)) return fail(LM_ENOMEM, "cannot allocate");
+    uint8_t* out = pinned ? reinterpret_cast<uint8_t*>(sg->mem) : df.as<uint8_t>();
+    hipStream_t s = sg ? sg->lane[0].s : nullptr;
+    const int32_t* dev_tracks = nullptr;
+    if (n_tracks <= LM_ARG_TRACKS) {
+        std::copy(tracks, tracks + n_tracks, rows.row);
+    } else {
+        if (dt.ensure((size_t)n_tracks * 4)) return fail(LM_ENOMEM, "cannot allocate");
+        HIP_TRY(hipMemcpy(dt.p, tracks, (size_t)n_tracks * 4, hipMemcpyHostToDevice));
+        dev_tracks = dt.as<int32_t>();
+    }
+    for (int64_t t0 = 0; t0 < n_tracks; t0 += per) {
+        const int64_t c = std::min<int64_t>(per, n_tracks - t0);
+        if (!dev_tracks && t0 > 0) std::copy(tracks + t0, tracks + t0 + c, rows.row);
+        LAUNCH_TRY(lm_launch_peaks(counts, nx, m->g.src_ny, rows,
+                                   dev_tracks ? dev_tracks + t0 : nullptr, c, k, out, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        if (pinned)
+            std::memcpy(flags + t0 * nx, out, (size_t)c * nx);
+        else
+            HIP_TRY(hipMemcpy(flags, out, (size_t)c * nx, hipMemcpyDeviceToHost));
+    }
     return ok();
 }
 
@@ -1529,14 +1586,18 @@ lm_status lm_find_peaks(lm_map* m, const int32_t* tracks, int32_t n_tracks, int3
 
 namespace {
 
-// Device buffers of one peak-statistics call: tracks (n_tracks int32), the bin
-// of every pixel column (src_nx int32), the bin edges (n_bins + 1 doubles) and
-// the two histograms (2 n_bins uint64).
+// Buffers of one peak-statistics call: rows and first columns of the bins in
+// device memory (null: passed by value), the two histograms (2 n_bins uint64)
+// and the count of finished workgroups, zero, and where the kernel writes the
+// sums: pinned memory, or device memory that is copied.
 struct PeakScratch {
     int32_t* tracks;
-    int32_t* bin_of;
-    double* edges;
+    int32_t* cols;
     unsigned long long* hist;
+    unsigned* done;
+    unsigned long long* out;
+    bool out_pinned;
+    hipStream_t s;
 };
 
 lm_status peak_stats_check(lm_map* m, const int32_t* tracks, int32_t n_tracks, int32_t k,
@@ -1559,41 +1620,71 @@ lm_status peak_stats_check(lm_map* m, const int32_t* tracks, int32_t n_tracks, i
     return LM_OK;
 }
 
-// The statistics proper, on device buffers the caller provides.  Light-curve
-// pixels per bin are counted on the host with the same column centres the
-// device bins by; the device does the peak test and the histograms.
-lm_status peak_stats_run(lm_map* m, const int32_t* tracks, int32_t n_tracks, int32_t k,
-                         const double* beta_edges, int32_t n_bins, uint64_t* peaks,
-                         uint64_t* heights, uint64_t* pixels, const PeakScratch& d)
+// First pixel column of each bin and the end of the last (n_bins + 1 values): the
+// columns p with edge b <= x0 + (p + 1/2) dx start there.  The centres, evaluated
+// in FP64 in that order, do not decrease with p.
+void bin_columns(const lm_geometry& g, const double* edges, int32_t n_bins, int32_t* col)
 {
-    const int64_t nx = m->g.src_nx;
-    std::fill(pixels, pixels + n_bins, 0);
-    for (int64_t p = 0; p < nx; ++p) {
-        const double bc = m->g.src_x0 + ((double)p + 0.5) * m->g.src_dx;
-        if (bc >= beta_edges[0] && bc < beta_edges[n_bins]) {
-            const int64_t b =
-                (std::upper_bound(beta_edges, beta_edges + n_bins + 1, bc) - beta_edges) - 1;
-            pixels[b] += (uint64_t)n_tracks;
+    for (int32_t b = 0; b <= n_bins; ++b) {
+        int64_t lo = b > 0 ? col[b - 1] : 0, hi = g.src_nx;
+        while (lo < hi) {
+            const int64_t p = lo + (hi - lo) / 2;
+            if (g.src_x0 + ((double)p + 0.5) * g.src_dx >= edges[b])
+                hi = p;
+            else
+                lo = p + 1;
         }
+        col[b] = (int32_t)lo;
     }
+}
+
+// The statistics proper, on buffers the caller provides; col as bin_columns.
+lm_status peak_stats_run(lm_map* m, const int32_t* tracks, int32_t n_tracks, int32_t k,
+                         const int32_t* col, int32_t n_bins, uint64_t* peaks, uint64_t* heights,
+                         const PeakScratch& d)
+{
+    HIP_TRY(hipDeviceSynchronize());
+    LmTracks rows{};
+    LmBins bins{};
+    if (d.tracks)
+        HIP_TRY(hipMemcpy(d.tracks, tracks, (size_t)n_tracks * 4, hipMemcpyHostToDevice));
+    else
+        std::copy(tracks, tracks + n_tracks, rows.row);
+    if (d.cols)
+        HIP_TRY(hipMemcpy(d.cols, col, (size_t)(n_bins + 1) * 4, hipMemcpyHostToDevice));
+    else
+        std::copy(col, col + n_bins + 1, bins.col);
+    LAUNCH_TRY(lm_launch_peak_stats(reinterpret_cast<const unsigned long long*>(m->counts),
+                                    m->g.src_nx, m->g.src_ny, rows, d.tracks, n_tracks, k, bins,
+                                    d.cols, col[0], col[n_bins], n_bins, d.hist, d.done, d.out,
+                                    d.s));
+    HIP_TRY(hipStreamSynchronize(d.s));
+    if (d.out_pinned) {
+        std::copy(d.out, d.out + n_bins, peaks);
+        std::copy(d.out + n_bins, d.out + 2 * (int64_t)n_bins, heights);
+    } else {
+        HIP_TRY(hipMemcpy(peaks, d.out, (size_t)n_bins * 8, hipMemcpyDeviceToHost));
+        HIP_TRY(hipMemcpy(heights, d.out + n_bins, (size_t)n_bins * 8, hipMemcpyDeviceToHost));
+    }
+    return ok();
+}
+
+// Bin columns, and what needs no device: the light-curve pixels per bin.
+lm_status peak_stats_begin(lm_map* m, int32_t n_tracks, const double* edges, int32_t n_bins,
+                           uint64_t* peaks, uint64_t* heights, uint64_t* pixels,
+                           std::vector<int32_t>& col)
+{
+    try {
+        col.resize((size_t)n_bins + 1);
+    } catch (const std::bad_alloc&) {
+        return fail(LM_ENOMEM, "cannot allocate the bins");
+    }
+    bin_columns(m->g, edges, n_bins, col.data());
+    for (int32_t b = 0; b < n_bins; ++b)
+        pixels[b] = (uint64_t)(col[b + 1] - col[b]) * (uint64_t)n_tracks;
     std::fill(peaks, peaks + n_bins, 0);
     std::fill(heights, heights + n_bins, 0);
-    if (n_tracks == 0) return ok();
-    lm_status st = use_device(m);
-    if (st) return st;
-    HIP_TRY(hipDeviceSynchronize());
-    HIP_TRY(hipMemcpy(d.tracks, tracks, (size_t)n_tracks * 4, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(d.edges, beta_edges, (size_t)(n_bins + 1) * 8, hipMemcpyHostToDevice));
-    LAUNCH_TRY(lm_launch_column_bins(m->g.src_x0, m->g.src_dx, nx, d.edges, n_bins, d.bin_of,
-                                     nullptr));
-    LAUNCH_TRY(lm_launch_fill_u64(d.hist, 2 * (int64_t)n_bins, 0ull, nullptr));
-    LAUNCH_TRY(lm_launch_peak_bins(reinterpret_cast<const unsigned long long*>(m->counts), nx,
-                                   m->g.src_ny, d.tracks, n_tracks, k, d.bin_of, d.hist,
-                                   d.hist + n_bins, nullptr));
-    HIP_TRY(hipStreamSynchronize(nullptr));
-    HIP_TRY(hipMemcpy(peaks, d.hist, (size_t)n_bins * 8, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(heights, d.hist + n_bins, (size_t)n_bins * 8, hipMemcpyDeviceToHost));
-    return ok();
+    return LM_OK;
 }
 
 }  // namespace
@@ -1609,13 +1700,34 @@ lm_status lm_peak_stats(lm_map* m, const int32_t* tracks, int32_t n_tracks, int3
     if (st) return st;
     st = use_device(m);
     if (st) return st;
-    DevBuf dt, db, de, dh;
-    if (dt.ensure((size_t)std::max(n_tracks, 1) * 4) || db.ensure((size_t)m->g.src_nx * 4) ||
-        de.ensure((size_t)(n_bins + 1) * 8) || dh.ensure((size_t)n_bins * 16))
+    std::vector<int32_t> col;
+    st = peak_stats_begin(m, n_tracks, beta_edges, n_bins, peaks, heights, pixels, col);
+    if (st) return st;
+    if (n_tracks == 0) return ok();
+    static_assert((size_t)kHistBins * 16 <= kStageBytes, "the sums fit the pinned memory");
+    StageUse sg(m->device);
+    DevBuf dt, dc, dh;
+    if ((n_tracks > LM_ARG_TRACKS && dt.ensure((size_t)n_tracks * 4)) ||
+        (n_bins > LM_ARG_BINS && dc.ensure((size_t)(n_bins + 1) * 4)))
         return fail(LM_ENOMEM, "cannot allocate");
-    return peak_stats_run(m, tracks, n_tracks, k, beta_edges, n_bins, peaks, heights, pixels,
-                          PeakScratch{dt.as<int32_t>(), db.as<int32_t>(), de.as<double>(),
-                                      dh.as<unsigned long long>()});
+    PeakScratch d{dt.as<int32_t>(), dc.as<int32_t>(), nullptr, nullptr, nullptr, false, nullptr};
+    if (sg) {
+        d.hist = reinterpret_cast<unsigned long long*>(sg->dev() + kHistOff);
+        d.done = reinterpret_cast<unsigned*>(sg->dev() + kDoneOff);
+        d.out = sg->mem;
+        d.out_pinned = true;
+        d.s = sg->lane[0].s;
+    } else {
+        if (dh.ensure((size_t)n_bins * 32 + 8)) return fail(LM_ENOMEM, "cannot allocate");
+        LAUNCH_TRY(lm_launch_fill_u64(dh.as<unsigned long long>(), 4 * (int64_t)n_bins + 1, 0ull,
+                                      nullptr));
+        d.hist = dh.as<unsigned long long>();
+        d.out = d.hist + 2 * (int64_t)n_bins;
+        d.done = reinterpret_cast<unsigned*>(d.out + 2 * (int64_t)n_bins);
+    }
+    st = peak_stats_run(m, tracks, n_tracks, k, col.data(), n_bins, peaks, heights, d);
+    if (st && sg) (void)sg->clear_hist();
+    return st;
 }
 
 lm_status lm_peak_stats_noalloc(lm_map* m, const int32_t* tracks, int32_t n_tracks, int32_t k,
@@ -1633,15 +1745,24 @@ lm_status lm_peak_stats_noalloc(lm_map* m, const int32_t* tracks, int32_t n_trac
                     n_bins);
     st = use_device(m);
     if (st) return st;
+    std::vector<int32_t> col;
+    st = peak_stats_begin(m, n_tracks, beta_edges, n_bins, peaks, heights, pixels, col);
+    if (st) return st;
+    if (n_tracks == 0) return ok();
     void* base = nullptr;
     LAUNCH_TRY(lm_scratch_address(&base));
     unsigned char* s = static_cast<unsigned char*>(base);
-    return peak_stats_run(m, tracks, n_tracks, k, beta_edges, n_bins, peaks, heights, pixels,
-                          PeakScratch{reinterpret_cast<int32_t*>(s),
-                                      reinterpret_cast<int32_t*>(s + LM_SCRATCH_OFF_BINOF),
-                                      reinterpret_cast<double*>(s + LM_SCRATCH_OFF_EDGES),
-                                      reinterpret_cast<unsigned long long*>(
-                                          s + LM_SCRATCH_OFF_HIST)});
+    const PeakScratch d{reinterpret_cast<int32_t*>(s),
+                        reinterpret_cast<int32_t*>(s + LM_SCRATCH_OFF_BINS),
+                        reinterpret_cast<unsigned long long*>(s + LM_SCRATCH_OFF_HIST),
+                        reinterpret_cast<unsigned*>(s + LM_SCRATCH_OFF_DONE),
+                        reinterpret_cast<unsigned long long*>(s + LM_SCRATCH_OFF_OUT),
+                        false,
+                        nullptr};
+    // the histograms are cleared at the start of each call
+    LAUNCH_TRY(lm_launch_fill_u64(d.hist, (LM_SCRATCH_OFF_OUT - LM_SCRATCH_OFF_HIST) / 8, 0ull,
+                                  nullptr));
+    return peak_stats_run(m, tracks, n_tracks, k, col.data(), n_bins, peaks, heights, d);
 }
 
 lm_status lm_fold_scales(double theta_e_arcsec, double d_x, double d_y, double kappa0,

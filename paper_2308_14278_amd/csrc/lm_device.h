@@ -1583,11 +1583,11 @@ template <int SCHEME, int PREC, int P>
 __global__ __launch_bounds__(kWG) void k_trace(LmDesc d, const int64_t* __restrict__ ii,
                                                const int64_t* __restrict__ jj, int64_t n,
                                                int32_t* __restrict__ po, int32_t* __restrict__ qo,
-                                               double* __restrict__ uv)
+                                               double* __restrict__ uv, LmUnits units)
 {
     const int64_t t = (int64_t)blockIdx.x * kWG + threadIdx.x;
     if (t >= n) return;
-    double* u = uv ? uv + 2 * t : nullptr;
+    double w[2], *u = uv ? w : nullptr;
     int32_t p, q;
     if (d.fold)
         trace_one<SCHEME, PREC, P, true>(d, ii[t], jj[t], p, q, u);
@@ -1596,6 +1596,11 @@ __global__ __launch_bounds__(kWG) void k_trace(LmDesc d, const int64_t* __restri
     if (po) {
         po[t] = p;
         qo[t] = q;
+    }
+    if (uv) {
+        // (the units' members are the host's, multiply and add rounded apart)
+        uv[2 * t] = units.beta ? units.x0 + w[0] * units.dx : w[0];
+        uv[2 * t + 1] = units.beta ? units.y0 + w[1] * units.dy : w[1];
     }
 }
 
@@ -1811,12 +1816,13 @@ struct TraceLauncher {
     int32_t* p;
     int32_t* q;
     double* uv;
+    const LmUnits& units;
     hipStream_t s;
     template <int S, int PR, int NR, int P>
     int go()
     {
         hipLaunchKernelGGL((k_trace<S, PR, P>), dim3((unsigned)((n + kWG - 1) / kWG)), dim3(kWG),
-                           0, s, d, ii, jj, n, p, q, uv);
+                           0, s, d, ii, jj, n, p, q, uv, units);
         return (int)hipGetLastError();
     }
 };

@@ -37,14 +37,17 @@ constexpr int window_bins(int prec, int layout, int rays_per_lane)
 }
 
 // Allocation-free peak statistics: limits and layout of the per-device scratch
-// array (tracks, column bins, two histograms; each part 256-byte aligned).
+// array (tracks, first columns of the bins, two histograms, the count of finished
+// workgroups; each part 256-byte aligned).  The two first hold less than the
+// limits on rows, columns and bins, which are the entry point's.
 #define LM_SCRATCH_TRACKS 8192
 #define LM_SCRATCH_COLS (1 << 20)
 #define LM_SCRATCH_BINS 4096
-#define LM_SCRATCH_OFF_BINOF (4 * LM_SCRATCH_TRACKS)
-#define LM_SCRATCH_OFF_EDGES (LM_SCRATCH_OFF_BINOF + 4 * LM_SCRATCH_COLS)
-#define LM_SCRATCH_OFF_HIST (LM_SCRATCH_OFF_EDGES + (8 * (LM_SCRATCH_BINS + 1) + 255) / 256 * 256)
-#define LM_SCRATCH_BYTES (LM_SCRATCH_OFF_HIST + 16 * LM_SCRATCH_BINS)
+#define LM_SCRATCH_OFF_BINS (4 * LM_SCRATCH_TRACKS)
+#define LM_SCRATCH_OFF_HIST (LM_SCRATCH_OFF_BINS + (4 * (LM_SCRATCH_BINS + 1) + 255) / 256 * 256)
+#define LM_SCRATCH_OFF_DONE (LM_SCRATCH_OFF_HIST + 16 * LM_SCRATCH_BINS)
+#define LM_SCRATCH_OFF_OUT (LM_SCRATCH_OFF_DONE + 256)
+#define LM_SCRATCH_BYTES (LM_SCRATCH_OFF_OUT + 16 * LM_SCRATCH_BINS)
 #define LM_MAX_DEVICES 64
 
 // Taylor coefficients of one level-2 cell: a_0 in FP64 (it carries the large
@@ -119,6 +122,29 @@ struct LmLensArrays {
     int32_t *lI, *lJ, *cell_start;
 };
 
+// What the probe's continuous coordinates come out in: pixels, or (beta) theta_E,
+// pixel coordinate u at x0 + u dx.
+struct LmUnits {
+    double x0 = 0, y0 = 0, dx = 1, dy = 1;
+    bool beta = false;
+    LmUnits() = default;
+    LmUnits(double x0_, double y0_, double dx_, double dy_, bool b)
+        : x0(x0_), y0(y0_), dx(dx_), dy(dy_), beta(b)
+    {
+    }
+};
+
+// Short lists passed by value: light-curve rows, and the first pixel column of
+// each bin and the end of the last.
+#define LM_ARG_TRACKS 64
+#define LM_ARG_BINS 511
+struct LmTracks {
+    int32_t row[LM_ARG_TRACKS];
+};
+struct LmBins {
+    int32_t col[LM_ARG_BINS + 1];
+};
+
 // Launchers implemented in lm_kernels.hip (return hipError_t as int).
 // Lens arrays from a pinned block: n x, y, m (doubles), n I and J, nstart CSR entries.
 int lm_launch_lens_upload(const double* src, int64_t n, int64_t nstart, const LmLensArrays& o,
@@ -161,20 +187,21 @@ int lm_launch_sum_u64(const unsigned long long* p, int64_t n, unsigned long long
 // coordinates, 2 per ray, that the pixels are the floor of
 int lm_launch_trace(const LmDesc& d, int scheme, int precision, int terms, const int64_t* ii,
                     const int64_t* jj, int64_t n, int32_t* p, int32_t* q, double* uv,
-                    void* stream);
+                    const LmUnits& units, void* stream);
 int lm_launch_deflect(const LmDesc& d, int scheme, int precision, int terms, const double* th,
                       int64_t n, double* alpha, void* stream);
-int lm_launch_peaks(const unsigned long long* counts, int64_t nx, int64_t ny,
+// Rows from `tracks`, or from `rows` where it is null (nt <= LM_ARG_TRACKS).
+int lm_launch_peaks(const unsigned long long* counts, int64_t nx, int64_t ny, const LmTracks& rows,
                     const int32_t* tracks, int64_t nt, int k, uint8_t* flags, void* stream);
-// bin_of[p] = b with edges[b] <= x0 + (p + 1/2) dx < edges[b+1] (FP64, multiply
-// and add each rounded to nearest), -1 outside [edges[0], edges[nb])
-int lm_launch_column_bins(double x0, double dx, int64_t nx, const double* edges, int nb,
-                          int32_t* bin_of, void* stream);
-// peaks[b] += true peaks of the listed rows in pixels j with bin_of[j] == b,
-// heights[b] += their counts (bin_of[j] < 0: no bin)
-int lm_launch_peak_bins(const unsigned long long* counts, int64_t nx, int64_t ny,
-                        const int32_t* tracks, int64_t nt, int k, const int32_t* bin_of,
-                        unsigned long long* peaks, unsigned long long* heights, void* stream);
+// out[b], out[nb + b] = true peaks of the listed rows in the columns [col[b],
+// col[b+1]) and the sum of their counts; col from `cols`, or from `bins` where it
+// is null (nb <= LM_ARG_BINS); c0 = col[0], c1 = col[nb].  hist (2 nb) and *done
+// are zero before and after.
+int lm_launch_peak_stats(const unsigned long long* counts, int64_t nx, int64_t ny,
+                         const LmTracks& rows, const int32_t* tracks, int64_t nt, int k,
+                         const LmBins& bins, const int32_t* cols, int c0, int c1, int nb,
+                         unsigned long long* hist, unsigned* done, unsigned long long* out,
+                         void* stream);
 int lm_shoot_occupancy(int scheme, int precision, int terms, int rays_per_lane, int layout,
                        int* wg_per_cu);
 // Device address of the current device's scratch array (resolved once per
@@ -195,7 +222,8 @@ bool lm_supported_rays_per_lane(int r);
     int LM_INST_CAT(lm_inst_occupancy, S, PR)(int nr, int terms, int layout, int* wg_per_cu); \
     int LM_INST_CAT(lm_inst_trace, S, PR)(const LmDesc& d, int terms, const int64_t* ii,      \
                                           const int64_t* jj, int64_t n, int32_t* p,           \
-                                          int32_t* q, double* uv, void* stream);              \
+                                          int32_t* q, double* uv, const LmUnits& units,       \
+                                          void* stream);                                      \
     int LM_INST_CAT(lm_inst_deflect, S, PR)(const LmDesc& d, int terms, const double* th,     \
                                             int64_t n, double* alpha, void* stream);
 LM_INST_DECLARE(0, 0)

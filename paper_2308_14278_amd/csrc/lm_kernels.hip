@@ -593,12 +593,13 @@ int lm_shoot_occupancy(int scheme, int precision, int terms, int rays_per_lane, 
 
 int lm_launch_trace(const LmDesc& d, int scheme, int precision, int terms, const int64_t* ii,
                     const int64_t* jj, int64_t n, int32_t* p, int32_t* q, double* uv,
-                    void* stream)
+                    const LmUnits& units, void* stream)
 {
     if (n <= 0) return 0;
 #define X(S, PR)                                                                            \
     if (scheme == S && precision == PR)                                                     \
-        return LM_INST_CAT(lm_inst_trace, S, PR)(d, terms, ii, jj, n, p, q, uv, stream);
+        return LM_INST_CAT(lm_inst_trace, S, PR)(d, terms, ii, jj, n, p, q, uv, units, \
+                                                 stream);
     LM_PAIRS(X)
 #undef X
     return (int)hipErrorInvalidValue;

@@ -34,9 +34,9 @@ int LM_INST_CAT(lm_inst_occupancy, LM_S, LM_PR)(int nr, int terms, int layout, i
 // the probes do not depend on the rays per lane
 int LM_INST_CAT(lm_inst_trace, LM_S, LM_PR)(const LmDesc& d, int terms, const int64_t* ii,
                                             const int64_t* jj, int64_t n, int32_t* p, int32_t* q,
-                                            double* uv, void* stream)
+                                            double* uv, const LmUnits& units, void* stream)
 {
-    TraceLauncher f{d, ii, jj, n, p, q, uv, (hipStream_t)stream};
+    TraceLauncher f{d, ii, jj, n, p, q, uv, units, (hipStream_t)stream};
     return dispatch_p<LM_S, LM_PR, 4>(terms, f);
 }
 
