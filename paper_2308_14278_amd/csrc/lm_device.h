@@ -54,13 +54,14 @@ struct UseTab {
     static constexpr bool value = SCHEME == 1;
 };
 
-// Waves per SIMD the shooting kernels must keep: the FP32 table paths are
-// issue-bound and need 4 (at most 128 VGPRs with 256-thread workgroups, 4 per
-// CU); the FP64 sums fit 3 (168 VGPRs; at the 220 they took without the hint
+// Waves per SIMD the shooting kernels must keep: the FP32 paths are issue-bound
+// and need 4 (at most 128 VGPRs with 256-thread workgroups, 4 per CU; the direct
+// sum over more lenses than one block spills its compensation between blocks for
+// it); the FP64 sums fit 3 (168 VGPRs; at the 220 they took without the hint
 // two waves ran).
 template <int SCHEME, int PREC>
 struct MinWaves {
-    static constexpr int value = SCHEME != 1 ? 1 : PREC == 2 ? 3 : 4;
+    static constexpr int value = SCHEME == 1 && PREC == 2 ? 3 : 4;
 };
 
 __device__ __forceinline__ void wave_sync_lds()
@@ -977,6 +978,46 @@ __device__ __forceinline__ void lens_loop(const T* tb, const L* lb, int nk, T py
     }
 }
 
+// Lenses lb[0..nb) against the NR rays of a lane without a table (direct sum):
+// the pair of `pair`, every ray's reciprocal its own, taken 8 columns at a time
+// with the reciprocals together at raised priority as in lens_loop, and the next
+// lens read one lens ahead.  Bound: vector issue (88% of the issue cycles of its
+// instructions).  100 lenses, 4096^2 rays: 309 us, 375 with the reciprocals one
+// by one at 3 workgroups per CU.
+template <int NR, class L>
+__device__ __forceinline__ void direct_loop(const L* lb, int nb, const float* px, float py,
+                                            float* bx, float* by)
+{
+    constexpr int S = NR < 8 ? NR : 8;
+    L next = lb[0];
+    for (int k = 0; k < nb; ++k) {
+        const L l = next;
+        next = lb[min(k + 1, nb - 1)];
+        const float dy = py - l.y;
+        const float dy2 = sq_floor(dy), mdy = l.w * dy;
+#pragma unroll
+        for (int o = 0; o < NR; o += S) {
+            float dx[S], w[S];
+#pragma unroll
+            for (int c = 0; c < S; ++c) {
+                dx[c] = px[o + c] - l.x;
+                w[c] = __builtin_fmaf(dx[c], dx[c], dy2);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+            for (int c = 0; c < S; ++c) w[c] = recip(w[c]);
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < S; ++c) {
+                bx[o + c] = __builtin_fmaf(dx[c], l.z * w[c], bx[o + c]);
+                by[o + c] = __builtin_fmaf(mdy, w[c], by[o + c]);
+            }
+        }
+    }
+}
+
 // One centred pair of the probes: the ray's column a, its partner column b
 // (the kernel's shared reciprocal) or, unpaired, a reciprocal of its own.
 template <bool PAIRED, class T>
@@ -1166,12 +1207,29 @@ __device__ __forceinline__ void process_unit(const LmDesc& d, int64_t ci, int64_
                 if (NEGY) ay[c] = -ay[c];
             }
         }
+        bool summed = false;
+        if constexpr (SCHEME == 0) {
+            if (nblk == 1) {
+                // one block of lenses: the first step of the compensated sum, whose
+                // compensation is not needed (and takes no registers)
+                T bx[NR], by[NR];
+#pragma unroll
+                for (int c = 0; c < NR; ++c) bx[c] = by[c] = 0;
+                direct_loop<NR>(lb, count, px, py, bx, by);
+#pragma unroll
+                for (int c = 0; c < NR; ++c) {
+                    ax[c] += bx[c];
+                    ay[c] += by[c];
+                }
+                summed = true;
+            }
+        }
 #pragma unroll
         for (int c = 0; c < NR; ++c) {
             kx[c] = 0;
             ky[c] = 0;
         }
-        for (int b = 0; b < nblk; ++b) {
+        for (int b = 0; b < nblk && !summed; ++b) {
             const int nb = __builtin_amdgcn_readfirstlane(min(kCap, count - b * kCap));
             if (nblk > 1) stage<SCHEME, PREC>(d, ci, cj, b * kCap, nb, zcx, zcy, lb, lane);
             T bx[NR], by[NR];
@@ -1199,14 +1257,7 @@ __device__ __forceinline__ void process_unit(const LmDesc& d, int64_t ci, int64_
                     wave_sync_lds();
                 }
             } else {
-#pragma unroll 2
-                for (int k = 0; k < nb; ++k) {
-                    const auto L = lb[k];
-                    const T dy = py - L.y;
-                    const T dy2 = sq_floor(dy), mdy = L.w * dy;
-#pragma unroll
-                    for (int c = 0; c < NR; ++c) pair(px[c], dy2, mdy, L.x, L.z, bx[c], by[c]);
-                }
+                direct_loop<NR>(lb, nb, px, py, bx, by);
             }
 #pragma unroll
             for (int c = 0; c < NR; ++c) {
@@ -1382,7 +1433,7 @@ __attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot
     ConstP<LmDesc> dp = (ConstP<LmDesc>)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(dp));
     const LmDesc& d = *(const LmDesc*)dp;
-    __shared__ unsigned win[window_bins(PREC, 0, NR)];
+    __shared__ unsigned win[window_bins(SCHEME, PREC, 0, NR)];
     __shared__ typename Prec<PREC>::L lens[LM_WAVES][Cap<SCHEME, 0>::value];
     __shared__ __align__(16) typename Prec<PREC>::T
         tab[LM_WAVES][UseTab<SCHEME, PREC>::value ? kLayTab[0] * tab_width(PREC) * NR : 1];
@@ -1408,7 +1459,7 @@ __attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot
                                                      const int32_t* __restrict__ order, int nmaps,
                                                      unsigned long long* queue)
 {
-    __shared__ unsigned win[window_bins(PREC, LAY, NR)];
+    __shared__ unsigned win[window_bins(SCHEME, PREC, LAY, NR)];
     __shared__ typename Prec<PREC>::L lens[LM_WAVES][Cap<SCHEME, LAY>::value];
     __shared__ __align__(16) typename Prec<PREC>::T
         tab[LM_WAVES][UseTab<SCHEME, PREC>::value ? kLayTab[LAY] * tab_width(PREC) * NR : 1];
@@ -1416,7 +1467,7 @@ __attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot
     const int tid = threadIdx.x, lane = tid & 63;
     // wave index as a scalar: everything derived from it stays uniform
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int b = tid; b < window_bins(PREC, LAY, NR); b += kWG) win[b] = 0u;
+    for (int b = tid; b < window_bins(SCHEME, PREC, LAY, NR); b += kWG) win[b] = 0u;
     const int64_t total = offs[nmaps];
     for (;;) {
         if (tid == 0) s_item = (long long)atomicAdd(queue, 1ull);

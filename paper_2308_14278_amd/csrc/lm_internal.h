@@ -28,12 +28,16 @@ static constexpr int kLayNear[LM_LAYOUTS] = {64, 64, 64, 32};
 constexpr int tab_width(int prec) { return prec == kPrecCentred ? 3 : 2; }
 
 // Window bins of a shooting kernel: the layout's, less what the wider table of
-// the centred sums takes (rays_per_lane columns per lens and wave), so that
-// the workgroup keeps to the layout's LDS budget.
-constexpr int window_bins(int prec, int layout, int rays_per_lane)
+// the centred sums takes (rays_per_lane columns per lens and wave); or what the
+// direct scheme's lens blocks leave of 40 KiB.  Either way the workgroup keeps to
+// the layout's LDS budget, four to a CU (the direct scheme on layout 0's window
+// took 43.5 KiB: three).
+constexpr int window_bins(int scheme, int prec, int layout, int rays_per_lane)
 {
-    return kLayWin[layout] -
-           (prec == kPrecCentred ? LM_WAVES * kLayTab[layout] * rays_per_lane : 0);
+    return scheme == 0 ? 6080
+                       : kLayWin[layout] - (prec == kPrecCentred
+                                                ? LM_WAVES * kLayTab[layout] * rays_per_lane
+                                                : 0);
 }
 
 // Allocation-free peak statistics: limits and layout of the per-device scratch
