@@ -170,37 +170,61 @@ __device__ __forceinline__ void box_centre(const LmDesc& d, int64_t I, int64_t J
     }
 }
 
+// Threads of step 1 below: the Q terms are cut into ns = ceil(Q / 8) slices of
+// eight, a box's lenses into ng = 256 / ns groups (group g holds every ng-th far
+// lens), and a thread sums SL consecutive slices of a group's lenses: all of them
+// up to five, else half, so that nsg threads share a group.
+struct L1Split {
+    int ns, ng, SL, nsg, boxes;
+};
+
+__host__ __device__ inline L1Split l1_split(int Q)
+{
+    L1Split f;
+    f.ns = (Q + 7) >> 3;
+    f.ng = kWG / f.ns;
+    f.nsg = f.ns <= 5 ? 1 : 2;
+    f.SL = (f.ns + f.nsg - 1) / f.nsg;
+    f.boxes = kWG / (f.ng * f.nsg);
+    return f;
+}
+
 // Hierarchical far field, step 1: the series of the far lenses of level-1 cell
 // (I, J) about the centre Z of one of its boxes, A_n = -sum_far m_k / (z_k -
 // Z)^(n+1), n < Q <= 64 (the level-2 series of Sec. 3.2.2 taken one level up).
-// One workgroup per box; the Q terms are cut into ns = ceil(Q / 8) slices of
-// eight, and the workgroup's threads into 256 / ns lens groups of ns threads
-// (thread s of a group sums terms 8 s .. 8 s + 7 over every (256 / ns)-th far
-// lens, so no thread idles on terms past Q); then threads n < Q add the
-// groups' partial sums in a fixed order.
-__global__ __launch_bounds__(kWG) void k_l1_expand(LmDesc d)
+// A workgroup takes as many boxes as its threads make (L1Split); then, box after
+// box, threads n < Q add the groups' partial sums in a fixed order.
+// Bound: FP64 issue.  A lens costs ~35 instructions for 1 / (z_k - Z) and its
+// eighth power and ~64 for each slice, the first of them once per thread: with
+// one slice per thread they were paid ns times (71115 boxes, 2749 lenses, Q = 24:
+// 1.75 ms, 2.66 so).
+template <int SL>
+__global__ __launch_bounds__(kWG) void k_l1_expand(LmDesc d, int64_t nboxes)
 {
-    __shared__ double2 part[8 * kWG];  // [groups][8 ns]
-    const int ns = (d.Q + 7) >> 3, ng = kWG / ns;
-    const int tid = threadIdx.x, grp = tid / ns, s = tid - grp * ns;
-    const int64_t cell = blockIdx.x;  // the box: row-major over [n1y nby][n1x nbx]
-    const int64_t bi = cell % (d.n1x * d.nbx), bj = cell / (d.n1x * d.nbx);
-    const int64_t I = bi / d.nbx, J = bj / d.nby;
-    double Zx, Zy;
-    box_centre(d, I, J, (int)(bi % d.nbx), (int)(bj % d.nby), Zx, Zy);
-    double ar[8], ai[8];
+    __shared__ double2 part[8 * kWG];  // [groups][8 ns] of one box
+    const L1Split f = l1_split(d.Q);
+    const int tid = threadIdx.x, per = f.ng * f.nsg;
+    const int mine = tid / per, sg = (tid - mine * per) / f.ng, grp = tid % f.ng;
+    const int64_t box0 = (int64_t)blockIdx.x * f.boxes;  // row-major over [n1y nby][n1x nbx]
+    const int64_t cell = box0 + mine;
+    const bool active = mine < f.boxes && cell < nboxes;
+    const int s0 = sg * SL;
+    double ar[8 * SL], ai[8 * SL];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < 8 * SL; ++j) {
         ar[j] = 0.0;
         ai[j] = 0.0;
     }
-    if (grp < ng) {
-        for (int64_t k = grp; k < d.nlens; k += ng) {
+    if (active) {
+        const int64_t bi = cell % (d.n1x * d.nbx), bj = cell / (d.n1x * d.nbx);
+        const int64_t I = bi / d.nbx, J = bj / d.nby;
+        double Zx, Zy;
+        box_centre(d, I, J, (int)(bi % d.nbx), (int)(bj % d.nby), Zx, Zy);
+        for (int64_t k = grp; k < d.nlens; k += f.ng) {
             if (abs(d.lI[k] - (int)I) <= d.H && abs(d.lJ[k] - (int)J) <= d.H) continue;
             const double wx = d.lx[k] - Zx, wy = d.ly[k] - Zy;
             const double iw2 = 1.0 / (wx * wx + wy * wy);
             const double ux = wx * iw2, uy = -wy * iw2;  // 1 / (z_k - Z)
-            // t = m u^(8 s + 1)
             double px = ux, py = uy;  // u^8 by three squarings
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
@@ -208,34 +232,48 @@ __global__ __launch_bounds__(kWG) void k_l1_expand(LmDesc d)
                 px = nx;
                 py = ny;
             }
-            double tx = d.lmd[k] * ux, ty = d.lmd[k] * uy;
-            for (int q = 0; q < s; ++q) {
-                const double nx = tx * px - ty * py, ny = tx * py + ty * px;
-                tx = nx;
-                ty = ny;
-            }
+            // first term of slice s: m u^(8 s + 1)
+            double bx = d.lmd[k] * ux, by = d.lmd[k] * uy;
+            auto next_slice = [&] {
+                const double nx = bx * px - by * py, ny = bx * py + by * px;
+                bx = nx;
+                by = ny;
+            };
+            for (int q = 0; q < s0; ++q) next_slice();
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                ar[j] -= tx;
-                ai[j] -= ty;
-                const double nx = tx * ux - ty * uy, ny = tx * uy + ty * ux;
-                tx = nx;
-                ty = ny;
+            for (int s = 0; s < SL; ++s) {
+                if (s > 0) next_slice();
+                double tx = bx, ty = by;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    ar[8 * s + j] -= tx;
+                    ai[8 * s + j] -= ty;
+                    const double nx = tx * ux - ty * uy, ny = tx * uy + ty * ux;
+                    tx = nx;
+                    ty = ny;
+                }
             }
         }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) part[8 * tid + j] = make_double2(ar[j], ai[j]);
     }
-    __syncthreads();
-    if (tid < d.Q) {
-        // term n of group g sits at 8 (g ns + n / 8) + n % 8 = 8 g ns + n
-        double sr = 0.0, si = 0.0;
-        for (int g = 0; g < ng; ++g) {
-            sr += part[8 * ns * g + tid].x;
-            si += part[8 * ns * g + tid].y;
+    for (int b = 0; b < f.boxes && box0 + b < nboxes; ++b) {
+        if (mine == b) {
+            // term n of group g sits at 8 ns g + n
+#pragma unroll
+            for (int j = 0; j < 8 * SL; ++j)
+                if (8 * s0 + j < 8 * f.ns)
+                    part[8 * (f.ns * grp + s0) + j] = make_double2(ar[j], ai[j]);
         }
-        d.l1exp[2 * (cell * d.Q + tid)] = sr;
-        d.l1exp[2 * (cell * d.Q + tid) + 1] = si;
+        __syncthreads();
+        if (tid < d.Q) {
+            double sr = 0.0, si = 0.0;
+            for (int g = 0; g < f.ng; ++g) {
+                sr += part[8 * f.ns * g + tid].x;
+                si += part[8 * f.ns * g + tid].y;
+            }
+            d.l1exp[2 * ((box0 + b) * d.Q + tid)] = sr;
+            d.l1exp[2 * ((box0 + b) * d.Q + tid) + 1] = si;
+        }
+        __syncthreads();
     }
 }
 
@@ -655,7 +693,15 @@ int lm_launch_coeffs_hier(const LmDesc& d, int terms, LmCoef* out, void* stream)
     if (n1 <= 0 || n2 <= 0) return 0;
     if (d.Q < terms || d.Q > 64) return (int)hipErrorInvalidValue;
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_l1_expand, dim3((unsigned)n1), dim3(kWG), 0, s, d);
+    const L1Split f = l1_split(d.Q);
+    const dim3 grid1((unsigned)((n1 + f.boxes - 1) / f.boxes));
+    switch (f.SL) {
+    case 1: hipLaunchKernelGGL(k_l1_expand<1>, grid1, dim3(kWG), 0, s, d, n1); break;
+    case 2: hipLaunchKernelGGL(k_l1_expand<2>, grid1, dim3(kWG), 0, s, d, n1); break;
+    case 3: hipLaunchKernelGGL(k_l1_expand<3>, grid1, dim3(kWG), 0, s, d, n1); break;
+    case 4: hipLaunchKernelGGL(k_l1_expand<4>, grid1, dim3(kWG), 0, s, d, n1); break;
+    default: hipLaunchKernelGGL(k_l1_expand<5>, grid1, dim3(kWG), 0, s, d, n1); break;
+    }
     const int e = (int)hipGetLastError();
     if (e) return e;
     const dim3 grid((unsigned)((n2 + kWG - 1) / kWG));

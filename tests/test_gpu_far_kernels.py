@@ -1,10 +1,13 @@
 """Far-field coefficients at the edges of their kernels against the oracle: the
 direct sums with waves that span several level-1 cells or wrap over lattice rows,
-lists with no far or no near lens, every number of terms and the FP32 form.
+lists with no far or no near lens, every number of terms and the FP32 form; the
+level-1 series at every split of its slices over threads.
 
 Tolerances: a_0 is a sum of at most 400 terms, each right to a few ulps, in FP64
 on both sides, so it agrees to 400 x 2^-53 < 1e-13 of the sum of the terms'
-sizes; 1e-11 covers it.  a_1.. are rounded to FP32 (2^-24).  The FP32 form's terms carry a few FP32 ulps each: 1e-5."""
+sizes; the re-expanded series multiplies that by at most 1 / (1 - rho)^4 < 20
+(rho <= 0.38).  1e-11 of the terms' sizes covers both.  a_1.. are rounded to FP32
+(2^-24).  The FP32 form's terms carry a few FP32 ulps each: 1e-5."""
 import numpy as np
 import pytest
 
@@ -64,3 +67,14 @@ def test_direct_coefficients(nx, ny, kx, ky, halo, terms, n, spread, oracle_lib)
 def test_direct_coefficients_fp32(oracle_lib):
     g = _geometry(700, 330, 3, 2, 1, 4, precision=lm.LM_PREC_FP32)
     _check(g, _lenses(g, 300, 2.0, 8), oracle_lib, tol=1e-5)
+
+
+@pytest.mark.parametrize("far_order,halo", [
+    (5, 60), (8, 12), (9, 12), (16, 3), (17, 3), (24, 1), (31, 1), (33, 1), (40, 1), (41, 1),
+    (48, 1), (49, 1), (56, 1), (57, 1), (64, 1)])
+def test_series_coefficients(far_order, halo, oracle_lib):
+    # square level-1 cells of 5 x 5: rho = sqrt(8) / (5 halo + 2.5)
+    g = _geometry(1280, 1280, 5, 5, halo, 4, far_order)
+    g.ray_dy = g.ray_dx
+    g.ray_y0 = -g.ray_dy * g.ray_ny / 2
+    _check(g, _lenses(g, 300, 6.0 + 8 * halo, far_order), oracle_lib)
