@@ -432,10 +432,6 @@ void rect_cells(int R, int64_t i0, int64_t j0, int64_t ni, int64_t nj, int64_t& 
 }
 
 // win_max: uint32 bins the kernel's LDS window holds (its layout's).
-// Rays per lane a kernel of precision prec runs when nr are asked for (the
-// centred sums run at most 8).
-int lanes_nr(int prec, int nr) { return prec == LM_PREC_MIXED_CENTRED && nr > 8 ? 8 : nr; }
-
 Exec choose_exec(const lm_map* m, int64_t ncells_x, int64_t ncells_y, int g_scale,
                  int win_max = kLayWin[0])
 {
@@ -1139,8 +1135,7 @@ lm_status lm_shoot(lm_map* m, int64_t i0, int64_t j0, int64_t ni, int64_t nj, vo
     if (st) return st;
     const int64_t R = m->g.coarse;
     const Exec e = choose_exec(m, (i0 + ni - 1) / R - i0 / R + 1, (j0 + nj - 1) / R - j0 / R + 1, 1,
-                               window_bins(m->g.scheme, m->prec, 0,
-                                           lanes_nr(m->prec, m->rays_per_lane)));
+                               window_bins(m->g.scheme, m->prec, 0, m->rays_per_lane));
     LmDesc d = make_desc(m, i0, j0, i0 + ni, j0 + nj, e);
     if (d.ntiles > 0x7fffffffLL) return fail(LM_EUNSUPPORTED, "too many workgroup tiles");
     LAUNCH_TRY(lm_launch_shoot_map(d, m->g.scheme, m->prec, m->g.taylor_terms,
@@ -1920,8 +1915,7 @@ lm_status batch_build(lm_batch* b, const std::vector<int64_t>& work)
         rect_cells(m->g.coarse, own[0], own[1], own[2], own[3], cx, cy);
         const Exec e = choose_exec(
             m, cx, cy, b->g_scale,
-            window_bins(m->g.scheme, m->prec, group_layout(b, m->prec),
-                        lanes_nr(m->prec, b->rays_per_lane)));
+            window_bins(m->g.scheme, m->prec, group_layout(b, m->prec), b->rays_per_lane));
         ds[k] = make_desc(m, r[0], r[1], r[0] + r[2], r[1] + r[3], e);
         if (r[2] == 0 || r[3] == 0) ds[k].ntiles = 0;
         if (ds[k].ntiles > 0x7fffffffLL)

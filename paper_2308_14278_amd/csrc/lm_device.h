@@ -905,12 +905,14 @@ __device__ __forceinline__ void row_base_px(const Row<PREC, P, FOLD>& rw, unsign
 // products and in front of the reciprocals of the step before (the last step
 // re-reads the last lens).  S = 8 in FP32 and 4 where an entry is wider (centred
 // sums, FP64) keeps both steps' entries within the registers of the waves per
-// SIMD of MinWaves.  And once its waves have mixed FP32 reciprocals into their
+// SIMD of MinWaves, at 16 rays per lane too (the centred sums, held to 8 rays
+// while a lens was taken whole, gained 6.5% from it: Table 1 band 116.9 and 109.3
+// ms).  And once its waves have mixed FP32 reciprocals into their
 // streams, a SIMD falls back to one instruction at a time: 8 reciprocals and 72
 // multiplies and FMAs per wave take 331 cycles, or 221 (8.3 per reciprocal and
 // 2.07 for the rest make 215) when the wave raises its priority around the
 // reciprocals.  Measured, shooting kernel before and after all of this: Table 1
-// band (centred) 120.3 and 113.3 ms, 110-lens lists (FP64) 51.5 and 47.5 ms, a
+// band (centred) 120.8 and 109.3 ms, 110-lens lists (FP64) 51.5 and 47.5 ms, a
 // 4e11-ray band at paper scale 480 and 473 ms (484 without the priority).
 template <int PREC, int NR, class L, class T>
 __device__ __forceinline__ void lens_loop(const T* tb, const L* lb, int nk, T py, T* bx, T* by)
@@ -1802,22 +1804,13 @@ int dispatch_p(int terms, F& f)
     }
 }
 
-// The centred sums run at most 8 rays per lane: with 16, their wider table
-// rows and the change of deflection need more than the 128 VGPRs of four waves
-// per SIMD.
 template <int S, int PR, class F>
 int dispatch_nr(int nr, int terms, F& f)
 {
     switch (nr) {
     case 4: return dispatch_p<S, PR, 4>(terms, f);
     case 8: return dispatch_p<S, PR, 8>(terms, f);
-    case 16:
-        // the centred sums need more registers per ray: 16 rays per lane would
-        // spill at 4 waves per SIMD, so they run 8
-        if constexpr (PR == kPrecCentred)
-            return dispatch_p<S, PR, 8>(terms, f);
-        else
-            return dispatch_p<S, PR, 16>(terms, f);
+    case 16: return dispatch_p<S, PR, 16>(terms, f);
     default: return (int)hipErrorInvalidValue;
     }
 }
