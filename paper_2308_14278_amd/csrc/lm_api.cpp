@@ -910,8 +910,8 @@ lm_status lm_create(const lm_geometry* g, lm_map** out)
         return fail(LM_ENOMEM, "cannot allocate %zu counts", npix);
     if (m->n_out.ensure(sizeof(uint64_t)) != hipSuccess) return fail(LM_ENOMEM, "cannot allocate n_out");
     m->counts = m->counts_own.as<uint64_t>();
-    LAUNCH_TRY(lm_launch_fill_u64((unsigned long long*)m->counts, (int64_t)npix, 0ull, nullptr));
-    LAUNCH_TRY(lm_launch_fill_u64(m->n_out.as<unsigned long long>(), 1, 0ull, nullptr));
+    LAUNCH_TRY(lm_launch_reset_counts((unsigned long long*)m->counts, (int64_t)npix,
+                                      m->n_out.as<unsigned long long>(), nullptr));
     HIP_TRY(hipStreamSynchronize(nullptr));
     // empty lens set
     st = lm_set_lenses(m.get(), nullptr, nullptr, nullptr, 0);
@@ -1353,9 +1353,9 @@ lm_status lm_reset_counts(lm_map* m, void* stream)
     lm_status st = use_device(m);
     if (st) return st;
     hipStream_t s = (hipStream_t)stream;
-    LAUNCH_TRY(lm_launch_fill_u64((unsigned long long*)m->counts,
-                                  (int64_t)m->g.src_nx * m->g.src_ny, 0ull, s));
-    LAUNCH_TRY(lm_launch_fill_u64(m->n_out.as<unsigned long long>(), 1, 0ull, s));
+    LAUNCH_TRY(lm_launch_reset_counts((unsigned long long*)m->counts,
+                                      (int64_t)m->g.src_nx * m->g.src_ny,
+                                      m->n_out.as<unsigned long long>(), s));
     m->n_shot = 0;
     m->has_counts = false;
     m->last = s;

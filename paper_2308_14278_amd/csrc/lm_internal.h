@@ -178,6 +178,8 @@ int lm_launch_shoot_batch(const LmDesc* descs, const int64_t* offsets, const int
                           int nmaps, unsigned long long* queue, int scheme, int precision,
                           int terms, int rays_per_lane, int layout, int grid, void* stream);
 int lm_launch_fill_u64(unsigned long long* p, int64_t n, unsigned long long v, void* stream);
+int lm_launch_reset_counts(unsigned long long* counts, int64_t n, unsigned long long* n_out,
+                           void* stream);
 // Entries [first, first + n) of a window of the map (np columns from (p0, q0);
 // whole: the map) to pinned host memory, as counts or (mu) counts x factor, and
 // *extra (may be null) after them.
