@@ -384,7 +384,6 @@ struct lm_map {
     bool has_counts = false;
     uint64_t n_shot = 0;
     hipStream_t last = nullptr;
-    int rays_per_lane = 16;
     // bumped by every call that changes what a batch's captured launches read
     // (lens buffers and count, macro model, counts buffer)
     uint64_t gen = 0;
@@ -410,6 +409,7 @@ lm_status use_device(const lm_map* m)
 // Work decomposition of a tile: cells per side, column chunks, window.
 struct Exec {
     int G = 1, ncc = 1, cw = 64, wx = 64, wy = 64;
+    int split = 1, nr = 16;  // single maps: workgroups to a tile, rays per lane
 };
 
 // Level-2 cells per side of a workgroup tile: about 512 rays per side times the
@@ -475,6 +475,31 @@ Exec choose_exec(const lm_map* m, int64_t ncells_x, int64_t ncells_y, int g_scal
     return e;
 }
 
+// Workgroups that the device holds at once (256 CUs, four each).
+constexpr int64_t kResident = 1024;
+
+// Splits the tiles of a small rectangle over more workgroups, each with shorter
+// column chunks and, below 16 columns, fewer rays per lane.  With less than one
+// wave per SIMD a launch lasts as long as one wave's chain over its columns and
+// lenses, and a split shortens the chain.  The line is where the workgroups still
+// run at once (us, unsplit -> split; direct unless noted):
+//   250 x 190 rays, 31 lenses     26.2 -> 18.0    700 x 400, 300    97.7 -> 52.6
+//   1000 x 1000, 100              52.0 -> 40.6    1400 x 1400, 300   142 -> 131
+//   interpolated, 12000 x 35      21.8 -> 20.6
+// and past it a second round costs what the chain saves or more (at 2048
+// workgroups 1400 x 1400 took 147, interpolated 57446 x 5 took 35 for 27).
+// A ray's sums do not depend on the split: the counts are the same.
+void split_tiles(Exec& e, int64_t tiles)
+{
+    if (e.G > 1) return;
+    while (2 * e.split * tiles <= kResident && e.cw % 8 == 0) {
+        e.split *= 2;
+        e.cw /= 2;
+    }
+    // a unit's columns are a multiple of its rays per lane: no step for padding
+    if (e.split > 1) e.nr = e.cw % 16 == 0 ? 16 : e.cw % 8 == 0 ? 8 : 4;
+}
+
 void split_ff(double v, float& hi, float& lo)
 {
     hi = (float)v;
@@ -531,6 +556,7 @@ LmDesc make_desc(const lm_map* m, int64_t i0, int64_t j0, int64_t i1, int64_t j1
     d.G = e.G;
     d.ncc = e.ncc;
     d.cw = e.cw;
+    d.split = e.split;
     d.nrb = g.coarse / 64;
     d.wx = e.wx;
     d.wy = e.wy;
@@ -1134,12 +1160,13 @@ lm_status lm_shoot(lm_map* m, int64_t i0, int64_t j0, int64_t ni, int64_t nj, vo
     st = resolve_precision(m, s);
     if (st) return st;
     const int64_t R = m->g.coarse;
-    const Exec e = choose_exec(m, (i0 + ni - 1) / R - i0 / R + 1, (j0 + nj - 1) / R - j0 / R + 1, 1,
-                               window_bins(m->g.scheme, m->prec, 0, m->rays_per_lane));
+    const int64_t cx = (i0 + ni - 1) / R - i0 / R + 1, cy = (j0 + nj - 1) / R - j0 / R + 1;
+    // fewer rays per lane leave no smaller a window
+    Exec e = choose_exec(m, cx, cy, 1, window_bins(m->g.scheme, m->prec, 0, Exec{}.nr));
+    split_tiles(e, cx * cy);
     LmDesc d = make_desc(m, i0, j0, i0 + ni, j0 + nj, e);
     if (d.ntiles > 0x7fffffffLL) return fail(LM_EUNSUPPORTED, "too many workgroup tiles");
-    LAUNCH_TRY(lm_launch_shoot_map(d, m->g.scheme, m->prec, m->g.taylor_terms,
-                                   m->rays_per_lane, s));
+    LAUNCH_TRY(lm_launch_shoot_map(d, m->g.scheme, m->prec, m->g.taylor_terms, e.nr, s));
     m->n_shot += (uint64_t)ni * (uint64_t)nj;
     m->has_counts = true;
     m->last = s;

@@ -1358,10 +1358,12 @@ __device__ __forceinline__ void tile_anchor(const LmDesc& d, int64_t cib, int64_
     ay0 = __builtin_amdgcn_readfirstlane((int)fy);
 }
 
+// part: which of the workgroups that share the tile this is (d.ncc column chunks of
+// each cell to each).
 template <int SCHEME, int PREC, int NR, int P, int LAY>
-__device__ __forceinline__ void process_tile(const LmDesc& d, int64_t t, int ax0, int ay0, unsigned* win,
-                             typename Prec<PREC>::L* lb, typename Prec<PREC>::T* tb, int wave,
-                             int lane)
+__device__ __forceinline__ void process_tile(const LmDesc& d, int64_t t, int part, int ax0, int ay0,
+                             unsigned* win, typename Prec<PREC>::L* lb,
+                             typename Prec<PREC>::T* tb, int wave, int lane)
 {
     const Win w{(unsigned)ax0, (unsigned)ay0, (unsigned)min(d.wx, d.snx - ax0),
                 (unsigned)min(d.wy, d.sny - ay0)};
@@ -1374,7 +1376,7 @@ __device__ __forceinline__ void process_tile(const LmDesc& d, int64_t t, int ax0
     unsigned nout = 0;
     for (int u = wave; u < U; u += LM_WAVES) {
         const int cu = u / per_cell, rem = u - cu * per_cell;
-        const int rb = rem / d.ncc, cc = rem - rb * d.ncc;
+        const int rb = rem / d.ncc, cc = rem - rb * d.ncc + part * d.ncc;
         const int64_t ci = cib + cu % d.G, cj = cjb + cu / d.G;
         if (ci >= d.ncx || cj >= d.ncy) continue;
         const int64_t cell_lo = ci * d.R, cell_hi = cell_lo + d.R;
@@ -1449,7 +1451,8 @@ __attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot
     int ax0, ay0;
     tile_anchor<SCHEME>(d, (d.tcx0 + tx) * d.G, (d.tcy0 + ty) * d.G, lane, ax0, ay0);
     __syncthreads();
-    process_tile<SCHEME, PREC, NR, P, 0>(d, t, ax0, ay0, win, lens[wave], tab[wave], wave, lane);
+    process_tile<SCHEME, PREC, NR, P, 0>(d, t, (int)blockIdx.y, ax0, ay0, win, lens[wave], tab[wave],
+                                         wave, lane);
     __syncthreads();
     flush_window(d, win, ax0, ay0, tid);
 }
@@ -1491,7 +1494,7 @@ __attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot
         const int64_t tx = (int)t % (int)d.ntx, ty = (int)t / (int)d.ntx;
         int ax0, ay0;
         tile_anchor<SCHEME>(d, (d.tcx0 + tx) * d.G, (d.tcy0 + ty) * d.G, lane, ax0, ay0);
-        process_tile<SCHEME, PREC, NR, P, LAY>(d, t, ax0, ay0, win, lens[wave], tab[wave], wave,
+        process_tile<SCHEME, PREC, NR, P, LAY>(d, t, 0, ax0, ay0, win, lens[wave], tab[wave], wave,
                                                lane);
         __syncthreads();
         flush_window(d, win, ax0, ay0, tid);
@@ -1738,7 +1741,8 @@ int launch_map_t(const LmDesc& d0, hipStream_t s)
     for (int64_t t0 = 0; t0 < d0.ntiles; t0 += kMaxGrid) {
         d.tile0 = t0;
         const int64_t n = d0.ntiles - t0 < kMaxGrid ? d0.ntiles - t0 : kMaxGrid;
-        hipLaunchKernelGGL((k_shoot_map<S, PR, NR, P>), dim3((unsigned)n), dim3(kWG), 0, s, d);
+        hipLaunchKernelGGL((k_shoot_map<S, PR, NR, P>), dim3((unsigned)n, (unsigned)d.split), dim3(kWG),
+                           0, s, d);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return (int)e;
     }

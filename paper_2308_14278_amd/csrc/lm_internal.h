@@ -90,7 +90,7 @@ struct LmDesc {
     // scheme and work decomposition
     int32_t R, Kx, Ky, H;
     int32_t G;                     // level-2 cells per workgroup-tile side
-    int32_t ncc;                   // column chunks per level-2 cell
+    int32_t ncc;                   // column chunks per level-2 cell and workgroup
     int32_t cw;                    // columns per chunk
     int32_t nrb;                   // 64-row blocks per level-2 cell (R / 64)
     int32_t wx, wy;                // LDS window (pixels)
@@ -117,6 +117,9 @@ struct LmDesc {
     double* l1exp;                 // [n1y nby][n1x nbx][Q] level-1 series per box, complex
     unsigned long long* counts;    // [sny][snx]
     unsigned long long* n_out;
+    // workgroups that share a tile in a k_shoot_map launch (its grid's y size), each
+    // with ncc column chunks of every cell
+    int32_t split;
 };
 
 // Device lens arrays of a map (LmDesc's, writable).
