@@ -10,10 +10,10 @@
 // walks its row NR columns at a time.  Every ray of a unit shares the cell's
 // near-lens list, which the wave stages once in its own LDS slice, so the
 // lens loop is uniform and reads lenses as LDS broadcasts.  Quantities that
-// are the same for all 64 rows -- the column offsets and their powers (scalar
-// loads), and per column and lens dx^2 and m dx (an LDS table the wave fills
-// 64 entries at a time) -- are computed once per wave, and the rays of columns
-// 2m and 2m+1 share one reciprocal per lens.
+// are the same for all 64 rows -- the column offsets and their powers, and
+// per column and lens dx^2 and m dx (LDS tables the wave fills 64 entries at a
+// time) -- are computed once per wave, and the rays of columns 2m and 2m+1 share
+// one reciprocal per lens.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -22,7 +22,6 @@
 #include "lm_internal.h"
 
 namespace {
-
 
 constexpr int kWG = LM_WG;
 

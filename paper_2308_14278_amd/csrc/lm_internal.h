@@ -42,8 +42,8 @@ constexpr int window_bins(int scheme, int prec, int layout, int rays_per_lane)
 
 // Allocation-free peak statistics: limits and layout of the per-device scratch
 // array (tracks, first columns of the bins, two histograms, the count of finished
-// workgroups; each part 256-byte aligned).  The two first hold less than the
-// limits on rows, columns and bins, which are the entry point's.
+// workgroups, the bins' results; each part 256-byte aligned).  LM_SCRATCH_COLS
+// is the entry point's limit on map columns; nothing of the array is per column.
 #define LM_SCRATCH_TRACKS 8192
 #define LM_SCRATCH_COLS (1 << 20)
 #define LM_SCRATCH_BINS 4096

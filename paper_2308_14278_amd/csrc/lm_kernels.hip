@@ -3,9 +3,8 @@
 // and the entry points that launch every kernel.
 //
 //  k_coeffs       far-field Taylor coefficients of every level-2 cell (Sec. 3.2.2):
-//                 a_n = -sum_{far k} m_k / (z_k - z_c)^(n+1); lens tiles staged
-//                 in LDS, FP64 arithmetic (FP64 FMA issues at the unpacked
-//                 FP32 rate on gfx950).
+//                 a_n = -sum_{far k} m_k / (z_k - z_c)^(n+1); ranges of far
+//                 lenses read through the scalar cache, FP64 arithmetic.
 //  k_l1_expand    hierarchical far field (optional): series per level-1 cell,
 //  k_l1_shift     re-expanded about every level-2 centre.
 //  k_sum_u64, k_fill_u64, k_reset_counts   reductions and fills of count buffers.
