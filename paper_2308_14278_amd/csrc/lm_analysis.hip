@@ -107,6 +107,11 @@ __global__ __launch_bounds__(256) void k_peak_stats(const unsigned long long* __
             }
             atomicAdd(&hist[lo], 1ull);
             atomicAdd(&hist[nb + lo], counts[i * nx + j]);
+            // a wave waits for its own additions: the barrier does not, and the fence
+            // before the count below waits for the first wave's alone.  Here, where
+            // additions are rare, it costs nothing measurable (flags and statistics
+            // of ten curves 58.6 us; with every wave's fence at the barrier 60.3)
+            __threadfence();
         }
     }
     __syncthreads();
