@@ -24,7 +24,7 @@ TARGET = "hipv4-amdgcn-amd-amdhsa--gfx950"
 
 def tools_available() -> bool:
     return all(os.path.exists(os.path.join(LLVM, t))
-               for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf"))
+               for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf", "llvm-objdump"))
 
 
 _BUNDLE_MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
@@ -109,3 +109,21 @@ def kernel_code_sha(symbol: str, lib: str = lensmap.LIB_PATH) -> str | None:
                 fh.seek(text[1] + (addr - text[0]))
                 return hashlib.sha256(fh.read(size)).hexdigest()[:16]
     return None
+
+
+def kernel_code(part: str, lib: str = lensmap.LIB_PATH) -> list[tuple[int, str, str]]:
+    """(address, instruction, note) of the first kernel whose symbol contains part;
+    the note of a branch names its target as <symbol+0x..>.  Empty if there is none."""
+    with tempfile.TemporaryDirectory() as tmp:
+        for co in _extract(lib, tmp):
+            syms = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--symbols", "-W", co],
+                                  check=True, capture_output=True, text=True).stdout
+            m = re.search(r" FUNC .* (\S*%s\S*)$" % part, syms, re.M)
+            if not m:
+                continue
+            text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn",
+                                   "--disassemble-symbols=" + m.group(1), co],
+                                  check=True, capture_output=True, text=True).stdout
+            return [(int(a, 16), ins, note) for ins, a, note in
+                    re.findall(r"^\s+(\S.*?)\s*// ([0-9A-F]+):(.*)$", text, re.M)]
+    return []

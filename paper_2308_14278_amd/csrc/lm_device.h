@@ -1148,6 +1148,18 @@ __device__ __forceinline__ void process_unit(const LmDesc& d, int64_t ci, int64_
     cell_base<SCHEME>(d, ci, cj, ubx, uby);
     float ar[P > 1 ? P : 1], ai[P > 1 ? P : 1], a0r = 0.f, a0i = 0.f;
     if (SCHEME == 1) load_taylor<P>(d, ci, cj, ar, ai, a0r, a0i);
+    if constexpr (SCHEME == 1 && PREC == 1) {
+        // the plain FP32 form evaluates the polynomial per ray: its coefficients, which
+        // come through the scalar cache, go into vector registers, since an FMA with a
+        // scalar operand takes twice the issue time (2e11 rays of the paper-scale
+        // lattice: 339.8 ms, 344.6 with scalar coefficients; 1.5e10 rays in cells of 128
+        // at P = 6: 19.7 and 20.3 ms)
+#pragma unroll
+        for (int n = 1; n < P; ++n) {
+            asm volatile("" : "+v"(ar[n]));
+            asm volatile("" : "+v"(ai[n]));
+        }
+    }
     const float zcxf = cell_cxf(d, ci), zcyf = cell_cyf(d, cj);
 
     // the lane's ray row

@@ -6,36 +6,17 @@ every wave's additions must have reached memory before its workgroup counts
 itself as finished.  One thread of one wave does that behind a barrier, and the
 barrier waits for no outstanding memory operation: each wave has to wait for its
 own before it."""
-import os
 import re
-import subprocess
-import tempfile
 
 import pytest
 
-import paper_2308_14278_amd.lensmap as lm
 from paper_2308_14278_amd import codeobj
-
-OBJDUMP = os.path.join(codeobj.LLVM, "llvm-objdump")
-
-
-def _kernel_code(part):
-    """(address, instruction text) of the one kernel whose symbol contains part."""
-    with tempfile.TemporaryDirectory() as tmp:
-        for co in codeobj._extract(lm.LIB_PATH, tmp):
-            text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", co], check=True,
-                                  capture_output=True, text=True).stdout
-            for body in re.split(r"\n(?=[0-9a-f]+ <)", text):
-                if re.match(r"[0-9a-f]+ <[^>]*%s" % part, body):
-                    return [(int(m.group(2), 16), m.group(1).strip(), m.group(3)) for m in
-                            re.finditer(r"^\s+(\S.*?)\s*// ([0-9A-F]+):(.*)$", body, re.M)]
-    return []
 
 
 def test_every_wave_waits_for_its_additions_before_the_barrier():
-    if not (codeobj.tools_available() and os.path.exists(OBJDUMP)):
+    if not codeobj.tools_available():
         pytest.skip("ROCm LLVM tools not found")
-    code = _kernel_code("k_peak_stats")
+    code = codeobj.kernel_code("k_peak_stats")
     assert code, "kernel not in the code object"
     at = {addr: k for k, (addr, _, _) in enumerate(code)}
     adds = [k for k, (_, ins, _) in enumerate(code) if ins.startswith("global_atomic_add_x2")]
