@@ -364,7 +364,7 @@ struct MapCount {
 struct lm_map {
     MapCount counted;
     lm_geometry g{};
-    int device = 0;
+    int device = 0, cus = 256;
     double kappa = 0, gamma = 0, kappa_star = 0;
     bool fold = false;
     double fold_dx = 0, fold_dy = 0;  // 1/theta_E
@@ -404,6 +404,13 @@ lm_status use_device(const lm_map* m)
     HIP_TRY(hipGetDevice(&cur));
     if (cur != m->device) HIP_TRY(hipSetDevice(m->device));
     return LM_OK;
+}
+
+int device_cus(int dev)
+{
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
+    return n > 0 ? n : 256;
 }
 
 // Work decomposition of a tile: cells per side, column chunks, window.
@@ -473,31 +480,6 @@ Exec choose_exec(const lm_map* m, int64_t ncells_x, int64_t ncells_y, int g_scal
     e.wx = wx;
     e.wy = wy;
     return e;
-}
-
-// Workgroups that the device holds at once (256 CUs, four each).
-constexpr int64_t kResident = 1024;
-
-// Splits the tiles of a small rectangle over more workgroups, each with shorter
-// column chunks and, below 16 columns, fewer rays per lane.  With less than one
-// wave per SIMD a launch lasts as long as one wave's chain over its columns and
-// lenses, and a split shortens the chain.  The line is where the workgroups still
-// run at once (us, unsplit -> split; direct unless noted):
-//   250 x 190 rays, 31 lenses     26.2 -> 18.0    700 x 400, 300    97.7 -> 52.6
-//   1000 x 1000, 100              52.0 -> 40.6    1400 x 1400, 300   142 -> 131
-//   interpolated, 12000 x 35      21.8 -> 20.6
-// and past it a second round costs what the chain saves or more (at 2048
-// workgroups 1400 x 1400 took 147, interpolated 57446 x 5 took 35 for 27).
-// A ray's sums do not depend on the split: the counts are the same.
-void split_tiles(Exec& e, int64_t tiles)
-{
-    if (e.G > 1) return;
-    while (2 * e.split * tiles <= kResident && e.cw % 8 == 0) {
-        e.split *= 2;
-        e.cw /= 2;
-    }
-    // a unit's columns are a multiple of its rays per lane: no step for padding
-    if (e.split > 1) e.nr = e.cw % 16 == 0 ? 16 : e.cw % 8 == 0 ? 8 : 4;
 }
 
 void split_ff(double v, float& hi, float& lo)
@@ -660,6 +642,26 @@ int64_t near_count(const lm_map* m, int64_t I, int64_t J)
         n += m->h_start[base + 2 * H + 1] - m->h_start[base];
     }
     return n;
+}
+
+// Mean and longest list of the level-1 cells a rectangle touches (direct sum: every
+// lens).
+void rect_lists(const lm_map* m, int64_t i0, int64_t j0, int64_t ni, int64_t nj, double& mean,
+                double& longest)
+{
+    const lm_geometry& g = m->g;
+    mean = longest = (double)m->nlens;
+    if (g.scheme == LM_SCHEME_DIRECT) return;
+    const int64_t sx = (int64_t)g.coarse * g.l1_kx, sy = (int64_t)g.coarse * g.l1_ky;
+    int64_t lenses = 0, cells = 0, most = 0;
+    for (int64_t J = j0 / sy; J <= (j0 + nj - 1) / sy; ++J)
+        for (int64_t I = i0 / sx; I <= (i0 + ni - 1) / sx; ++I, ++cells) {
+            const int64_t n = near_count(m, I, J);
+            lenses += n;
+            most = std::max(most, n);
+        }
+    mean = (double)lenses / (double)cells;
+    longest = (double)most;
 }
 
 // Mean near-list length over the rays of the whole lattice.
@@ -920,6 +922,7 @@ lm_status lm_create(const lm_geometry* g, lm_map** out)
     if (!m) return fail(LM_ENOMEM, "out of host memory");
     m->g = *g;
     HIP_TRY(hipGetDevice(&m->device));
+    m->cus = device_cus(m->device);
     m->ncx = ceil_div(g->ray_nx, g->coarse);
     m->ncy = ceil_div(g->ray_ny, g->coarse);
     if (g->scheme == LM_SCHEME_INTERP) {
@@ -1163,7 +1166,15 @@ lm_status lm_shoot(lm_map* m, int64_t i0, int64_t j0, int64_t ni, int64_t nj, vo
     const int64_t cx = (i0 + ni - 1) / R - i0 / R + 1, cy = (j0 + nj - 1) / R - j0 / R + 1;
     // fewer rays per lane leave no smaller a window
     Exec e = choose_exec(m, cx, cy, 1, window_bins(m->g.scheme, m->prec, 0, Exec{}.nr));
-    split_tiles(e, cx * cy);
+    // (lists matter to rectangles of few cells, which lie in few level-1 cells)
+    double list = 0.0, longest = 0.0;
+    if (e.G == 1 && cx * cy <= 8 * m->cus) rect_lists(m, i0, j0, ni, nj, list, longest);
+    const int form = m->g.scheme == LM_SCHEME_DIRECT ? 0 : m->prec == LM_PREC_MIXED_FP64 ? 2 : 1;
+    const LmSplit sp = lm_split(form, m->g.coarse, e.ncc, e.cw, e.G, cx * cy, ni, nj, list, longest,
+                                m->cus);
+    e.split = sp.split;
+    e.cw = sp.cw;
+    e.nr = sp.nr;
     LmDesc d = make_desc(m, i0, j0, i0 + ni, j0 + nj, e);
     if (d.ntiles > 0x7fffffffLL) return fail(LM_EUNSUPPORTED, "too many workgroup tiles");
     LAUNCH_TRY(lm_launch_shoot_map(d, m->g.scheme, m->prec, m->g.taylor_terms, e.nr, s));
@@ -1912,13 +1923,6 @@ bool layout_built(const lm_batch* b, int nr, int layout)
     return layout == 0 ||
            (layout > 0 && layout < LM_LAYOUTS && b->scheme == LM_SCHEME_INTERP && b->terms == 4 &&
             (nr == 8 || nr == 16));
-}
-
-int device_cus(int dev)
-{
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
-    return n > 0 ? n : 256;
 }
 
 // Build descriptors, cost order and queue offsets of every precision group and

@@ -122,6 +122,74 @@ struct LmDesc {
     int32_t split;
 };
 
+// How a launch for one map shares its tiles out: workgroups to a tile, columns per
+// chunk of a cell, rays per lane.
+struct LmSplit {
+    int split, cw, nr;
+};
+
+// Tiles of a small rectangle are shared by several workgroups, each with shorter
+// column chunks and, below 16 columns, fewer rays per lane: with one or two waves
+// per SIMD a launch lasts as long as one wave's chain over its columns and lenses,
+// which a split shortens.  A ray's sums do not depend on the split: the counts are
+// the same.
+//
+// form: 0 direct, 1 FP32 near sums, 2 FP64; R, ncc, cw: rays a side, column chunks and
+// columns per chunk of a cell; tiles of G x G cells (more than one: not split); ni x nj
+// rays; list, longest: mean and longest list of lenses; cus: CUs.
+//
+// The split and the rays per lane are those of the least time in a model of the
+// launch: a wave's steps of nr columns, each lens of the longest list taking `lat` ns
+// alone or, with k waves on its SIMD, each of a mean list k times `issue` (lists
+// counted `col` lenses longer, for starting and counting the columns), and 25 ns for
+// each workgroup, whose window is cleared and flushed.  The figures are fits to
+// launches of 4 to 2048 workgroups, among them (us, 1, 2 and 4 workgroups to a tile
+// of 64 x 64 rays):
+//   direct  250 x 190 rays,    30 lenses  20.1  14.9  12.3      300  87.0 55.0 38.1
+//           1000 x 1000,       10         19.8  21.8  30.6      300  91.4 72.8 69.9
+//           1400 x 1400,       10         26.0  30.6  49.8      300  122  115  125
+//   FP32    1000 x 1000,       10 near    17.0  21.4  32.9      300  90.4 70.2 70.4
+//           1400 x 1400,       10         21.6  29.9  51.7      300  101  103  126
+//   FP64    1000 x 1000,       10         18.7  21.7  36.2      300  120  101  115
+// and of 128 x 128 rays, 1, 2, 4 and 8 (FP32):
+//           1000 x 1000,       10 near    29.6  20.0  16.9 21.1 300  323  168  91.7 70.8
+//           2000 x 2000,       10         29.2  25.9  33.5 58.3 300  325  191  166  183
+inline LmSplit lm_split(int form, int R, int ncc, int cw, int G, int64_t tiles, int64_t ni,
+                        int64_t nj, double list, double longest, int cus)
+{
+    constexpr double lat[3][3] = {{254, 151, 98}, {255, 160, 115}, {360, 204, 139}};
+    constexpr double issue[3][3] = {{125, 72, 34}, {114, 62, 33}, {237, 122, 71}};
+    constexpr double col = 6.0;
+    const auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const int64_t rows = up(nj < R ? nj : R, 64);  // row blocks in use
+    LmSplit best{1, cw, 16};
+    double least = 0.0;
+    for (int s = 1; s == 1 || (G == 1 && cw % (4 * s) == 0 && s * tiles <= 8 * cus); s *= 2) {
+        const int c = cw / s;
+        const int64_t ncol = ni + 1 < c ? ni + 1 : c;  // (one more may make the first even)
+        const int64_t chunks = up(ni < R ? ni : R, c);  // in use
+        const int64_t units = rows * (chunks < ncc ? chunks : ncc);  // of a workgroup
+        // waves per SIMD
+        const double k = G > 1 ? 4.0
+                               : (double)up(tiles * up(chunks, ncc), cus) *
+                                     (double)(units < LM_WAVES ? units : LM_WAVES) / LM_WAVES;
+        for (int q = 0; q < 3; ++q) {
+            const int nr = 16 >> q;
+            const double alone = lat[form][q] * (longest + col);
+            const double shared = k * issue[form][q] * (list + col);
+            const double t =
+                (double)(up(units, LM_WAVES) * up(ncol, nr)) * (alone > shared ? alone : shared) +
+                25.0 * (double)(s * tiles);
+            // (a per cent of a model is worth no more workgroups or steps)
+            if ((s == 1 && q == 0) || t < 0.985 * least) {
+                least = t;
+                best = LmSplit{s, c, nr};
+            }
+        }
+    }
+    return best;
+}
+
 // Device lens arrays of a map (LmDesc's, writable).
 struct LmLensArrays {
     double *lx, *ly, *lmd;
