@@ -1168,8 +1168,9 @@ lm_status lm_shoot(lm_map* m, int64_t i0, int64_t j0, int64_t ni, int64_t nj, vo
     Exec e = choose_exec(m, cx, cy, 1, window_bins(m->g.scheme, m->prec, 0, Exec{}.nr));
     // (lists matter to rectangles of few cells, which lie in few level-1 cells)
     double list = 0.0, longest = 0.0;
-    if (e.G == 1 && cx * cy <= 8 * m->cus) rect_lists(m, i0, j0, ni, nj, list, longest);
     const int form = m->g.scheme == LM_SCHEME_DIRECT ? 0 : m->prec == LM_PREC_MIXED_FP64 ? 2 : 1;
+    if (form == 0 || (e.G == 1 && cx * cy <= 8 * m->cus))
+        rect_lists(m, i0, j0, ni, nj, list, longest);
     const LmSplit sp = lm_split(form, m->g.coarse, e.ncc, e.cw, e.G, cx * cy, ni, nj, list, longest,
                                 m->cus);
     e.split = sp.split;
@@ -1889,6 +1890,7 @@ struct lm_batch {
     std::vector<uint64_t> gens; // each map's generation when the graphs were built
     int scheme = 0, terms = 4, device = 0;
     int rays_per_lane = 16, g_scale = 1, wg_per_cu = 0;
+    int nr = 16;  // rays per lane of the built tables' launches (rays_per_lane, or lm_direct_nr)
     int layout = 0;             // LDS layout of the LM_PREC_MIXED group (others use 0)
     DevBuf descs;               // one LmDesc per map
     BatchGroup grp[kGroups];    // indexed by precision
@@ -1936,6 +1938,9 @@ lm_status batch_build(lm_batch* b, const std::vector<int64_t>& work)
         lm_status st = resolve_precision(m, b->cap);
         if (st) return st;
     }
+    b->nr = b->rays_per_lane;
+    if (b->scheme == LM_SCHEME_DIRECT)
+        for (lm_map* m : b->maps) b->nr = lm_direct_nr(b->nr, m->nlens);
     std::vector<LmDesc> ds(n);
     std::vector<double> cost(n);
     for (int k = 0; k < n; ++k) {
@@ -1946,7 +1951,7 @@ lm_status batch_build(lm_batch* b, const std::vector<int64_t>& work)
         rect_cells(m->g.coarse, own[0], own[1], own[2], own[3], cx, cy);
         const Exec e = choose_exec(
             m, cx, cy, b->g_scale,
-            window_bins(m->g.scheme, m->prec, group_layout(b, m->prec), b->rays_per_lane));
+            window_bins(m->g.scheme, m->prec, group_layout(b, m->prec), b->nr));
         ds[k] = make_desc(m, r[0], r[1], r[0] + r[2], r[1] + r[3], e);
         if (r[2] == 0 || r[3] == 0) ds[k].ntiles = 0;
         if (ds[k].ntiles > 0x7fffffffLL)
@@ -1977,8 +1982,8 @@ lm_status batch_build(lm_batch* b, const std::vector<int64_t>& work)
         HIP_TRY(hipMemcpy(G.offs.p, offs.data(), (G.nmaps + 1) * 8, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(G.order.p, order.data(), G.nmaps * 4, hipMemcpyHostToDevice));
         int occ = 0;
-        LAUNCH_TRY(lm_shoot_occupancy(b->scheme, pr, b->terms, b->rays_per_lane,
-                                      group_layout(b, pr), &occ));
+        LAUNCH_TRY(
+            lm_shoot_occupancy(b->scheme, pr, b->terms, b->nr, group_layout(b, pr), &occ));
         if (occ <= 0) occ = 1;
         const int wg = b->wg_per_cu > 0 ? std::min(b->wg_per_cu, occ) : occ;
         G.grid = device_cus(b->device) * wg;
@@ -2007,8 +2012,7 @@ lm_status batch_enqueue(lm_batch* b, hipStream_t s, bool with_coeffs, bool pre =
             LAUNCH_TRY(lm_launch_shoot_batch(b->descs.as<LmDesc>(), G.offs.as<int64_t>(),
                                              G.order.as<int32_t>(), G.nmaps,
                                              b->queue.as<unsigned long long>() + pr, b->scheme,
-                                             pr, b->terms, b->rays_per_lane, group_layout(b, pr),
-                                             G.grid, s));
+                                             pr, b->terms, b->nr, group_layout(b, pr), G.grid, s));
         }
     return LM_OK;
 }

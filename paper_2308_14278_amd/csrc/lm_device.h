@@ -32,6 +32,17 @@ struct Cap {
     static constexpr int value = SCHEME == 0 ? LM_LENS_CAP : kLayNear[LAY];
 };
 
+// Direct sum with 16 rays per lane: lists of one block only, so that no instance
+// holds the compensation of several blocks beside 16 rays: that spilled 107 registers
+// to scratch memory, whose set-up alone cost a launch of few lenses 2 us (us, one lens
+// 1400 x 1400 rays: 24.3 and 18.0; 200 lenses, 2000 x 2000: 142 and 131).  Longer lists
+// run 8 (lm_direct_nr), as fast as 16 with the spills (1000 lenses, 4000 x 4000: 2449
+// and 2406 us), in plain FP32 4% slower.
+template <int SCHEME, int NR>
+struct OneBlock {
+    static constexpr bool value = SCHEME == 0 && NR == 16;
+};
+
 // Arithmetic of the ray-lens pairs: FP32 (rebased or plain global) or FP64
 // (rebased), and the staged lens record of each.
 template <int PREC>
@@ -54,9 +65,7 @@ struct UseTab {
 };
 
 // Waves per SIMD the shooting kernels must keep: the FP32 paths are issue-bound
-// and need 4 (at most 128 VGPRs with 256-thread workgroups, 4 per CU; the direct
-// sum over more lenses than one block spills its compensation between blocks for
-// it); the FP64 sums fit 3 (168 VGPRs; at the 220 they took without the hint
+// and need 4 (at most 128 VGPRs with 256-thread workgroups, 4 per CU); the FP64 sums fit 3 (168 VGPRs; at the 220 they took without the hint
 // two waves ran).
 template <int SCHEME, int PREC>
 struct MinWaves {
@@ -1195,6 +1204,17 @@ __device__ __forceinline__ void process_unit(const LmDesc& d, int64_t ci, int64_
         constexpr bool POW = UseTab<SCHEME, PREC>::value && PREC != 1;
         static_assert(!POW || (D + CENT) * NR <= kTabCh * TW * NR, "powers exceed the table");
         T px[NR], ax[NR], ay[NR], kx[NR], ky[NR];
+        // start of the rays, from the powers of their own offsets px
+        auto start = [&] {
+#pragma unroll
+            for (int c = 0; c < NR; ++c) {
+                T pw[D];
+                col_powers<D>(px[c], pw);
+                ray_start<PREC, P, FOLD>(rw, pw, ax[c], ay[c]);
+                if (NEGX) ax[c] = -ax[c];
+                if (NEGY) ay[c] = -ay[c];
+            }
+        };
         T pxl = 0;  // offset of this lane's column in the wave's tables: NR divides 64
         if constexpr (UseTab<SCHEME, PREC>::value)
             pxl = column_offset<PREC>(d, c0 + (lane & (NR - 1)), ci);
@@ -1211,38 +1231,33 @@ __device__ __forceinline__ void process_unit(const LmDesc& d, int64_t ci, int64_
             table_start<NEGX, NEGY, PREC, P, FOLD, NR>(tb, rw, ax, ay);
         } else {
 #pragma unroll
-            for (int c = 0; c < NR; ++c) {
-                T pw[D];
-                px[c] = column_offset<PREC>(d, c0 + c, ci);
-                col_powers<D>(px[c], pw);
-                ray_start<PREC, P, FOLD>(rw, pw, ax[c], ay[c]);
-                if (NEGX) ax[c] = -ax[c];
-                if (NEGY) ay[c] = -ay[c];
-            }
+            for (int c = 0; c < NR; ++c) px[c] = column_offset<PREC>(d, c0 + c, ci);
         }
-        bool summed = false;
+        // direct sum over one block of lenses: the first step of the compensated sum,
+        // whose compensation is not needed; the rays start after their lenses, so that
+        // neither takes registers in the lens loop
+        const bool one = SCHEME == 0 && (OneBlock<SCHEME, NR>::value || nblk <= 1);
         if constexpr (SCHEME == 0) {
-            if (nblk == 1) {
-                // one block of lenses: the first step of the compensated sum, whose
-                // compensation is not needed (and takes no registers)
+            if (one) {
                 T bx[NR], by[NR];
 #pragma unroll
                 for (int c = 0; c < NR; ++c) bx[c] = by[c] = 0;
                 direct_loop<NR>(lb, count, px, py, bx, by);
+                start();
 #pragma unroll
                 for (int c = 0; c < NR; ++c) {
                     ax[c] += bx[c];
                     ay[c] += by[c];
                 }
-                summed = true;
             }
         }
+        if (!POW && !one) start();
 #pragma unroll
         for (int c = 0; c < NR; ++c) {
             kx[c] = 0;
             ky[c] = 0;
         }
-        for (int b = 0; b < nblk && !summed; ++b) {
+        for (int b = 0; b < nblk && !one; ++b) {
             const int nb = __builtin_amdgcn_readfirstlane(min(kCap, count - b * kCap));
             if (nblk > 1) stage<SCHEME, PREC>(d, ci, cj, b * kCap, nb, zcx, zcy, lb, lane);
             T bx[NR], by[NR];
@@ -1439,15 +1454,16 @@ __device__ __forceinline__ void flush_window(const LmDesc& d, unsigned* win, int
 
 template <int SCHEME, int PREC, int NR, int P>
 __global__ __launch_bounds__(kWG)
-__attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot_map(LmDesc)
+__attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot_map(LmDesc arg)
 {
-    // the descriptor, the kernel's only argument, read where it is used: as an
-    // argument by name its fields are loaded at the start and kept, which spills
-    // ~75 scalar registers into vector lanes and, at 16 rays per lane, vector
-    // registers to scratch
+    // The interpolated scheme reads the descriptor, the kernel's only argument, where
+    // it is used: as an argument by name its fields are loaded at the start and kept,
+    // which spills ~75 scalar registers into vector lanes and, at 16 rays per lane,
+    // vector registers to scratch.  The direct sum has the registers, and a launch of
+    // few lenses is 1 us shorter for them (1400 x 1400 rays, 10 lenses: 20.9 and 20.3).
     ConstP<LmDesc> dp = (ConstP<LmDesc>)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(dp));
-    const LmDesc& d = *(const LmDesc*)dp;
+    if constexpr (SCHEME == 1) asm volatile("" : "+s"(dp));
+    const LmDesc& d = SCHEME == 1 ? *(const LmDesc*)dp : arg;
     __shared__ unsigned win[window_bins(SCHEME, PREC, 0, NR)];
     __shared__ typename Prec<PREC>::L lens[LM_WAVES][Cap<SCHEME, 0>::value];
     __shared__ __align__(16) typename Prec<PREC>::T

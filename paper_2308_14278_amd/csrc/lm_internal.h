@@ -122,6 +122,10 @@ struct LmDesc {
     int32_t split;
 };
 
+// Rays per lane of a direct sum over nlens lenses when nr are asked for: its kernels
+// for 16 take one block of lenses.
+constexpr int lm_direct_nr(int nr, int64_t nlens) { return nlens > LM_LENS_CAP && nr > 8 ? 8 : nr; }
+
 // How a launch for one map shares its tiles out: workgroups to a tile, columns per
 // chunk of a cell, rays per lane.
 struct LmSplit {
@@ -158,7 +162,7 @@ inline LmSplit lm_split(int form, int R, int ncc, int cw, int G, int64_t tiles, 
                         int64_t nj, double list, double longest, int cus)
 {
     constexpr double lat[3][3] = {{254, 151, 98}, {255, 160, 115}, {360, 204, 139}};
-    constexpr double issue[3][3] = {{125, 72, 34}, {114, 62, 33}, {237, 122, 71}};
+    constexpr double issue[3][3] = {{125, 72, 40}, {114, 62, 33}, {237, 122, 71}};
     constexpr double col = 6.0;
     const auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
     const int64_t rows = up(nj < R ? nj : R, 64);  // row blocks in use
@@ -173,15 +177,15 @@ inline LmSplit lm_split(int form, int R, int ncc, int cw, int G, int64_t tiles, 
         const double k = G > 1 ? 4.0
                                : (double)up(tiles * up(chunks, ncc), cus) *
                                      (double)(units < LM_WAVES ? units : LM_WAVES) / LM_WAVES;
-        for (int q = 0; q < 3; ++q) {
-            const int nr = 16 >> q;
+        for (int q = form == 0 && longest > LM_LENS_CAP; q < 3; ++q) {
+            const int nr = 16 >> q;  // (lm_direct_nr)
             const double alone = lat[form][q] * (longest + col);
             const double shared = k * issue[form][q] * (list + col);
             const double t =
                 (double)(up(units, LM_WAVES) * up(ncol, nr)) * (alone > shared ? alone : shared) +
                 25.0 * (double)(s * tiles);
             // (a per cent of a model is worth no more workgroups or steps)
-            if ((s == 1 && q == 0) || t < 0.985 * least) {
+            if (least == 0.0 || t < 0.985 * least) {
                 least = t;
                 best = LmSplit{s, c, nr};
             }

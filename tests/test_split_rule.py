@@ -72,9 +72,9 @@ def test_the_longest_list_makes_the_chain(rule):
 
 @pytest.mark.parametrize("form", [DIRECT, FP32, FP64])
 def test_large_tiles_and_launches_stay_whole(rule, form):
-    assert rule(form, 64, 1000, 1000, 300, G=2) == (1, 16, 16)
+    assert rule(form, 64, 1000, 1000, 200, G=2) == (1, 16, 16)
     for R in (64, 128, 192, 320, 512):
-        split, cw, nr = rule(form, R, 400 * R, 30 * R, 300)
+        split, cw, nr = rule(form, R, 400 * R, 30 * R, 200)
         assert split == 1 and nr == 16
 
 
@@ -93,3 +93,11 @@ def test_chunks_cover_the_cells(rule, form, cus):
 @pytest.mark.parametrize("ni,nr", [(1, 4), (3, 4), (4, 8), (5, 8), (7, 8)])
 def test_narrow_rectangles_run_fewer_rays_per_lane(rule, form, ni, nr):
     assert rule(form, 320, ni, 700 * 320, 0) == (1, 80, nr)
+
+
+@pytest.mark.parametrize("lens,most", [(256, 16), (257, 8), (100000, 8)])
+def test_long_direct_lists_run_eight_rays_per_lane(rule, lens, most):
+    """The direct kernels for 16 rays per lane take one block of lenses."""
+    got = [rule(DIRECT, R, ni, nj, lens, G=G)[2] for R in (64, 128, 512) for G in (1, 4)
+           for ni, nj in ((1, 1), (9, 700), (1000, 1000), (9000, 9000), (100 * R, 100 * R))]
+    assert max(got) == most
