@@ -48,8 +48,12 @@ __device__ __forceinline__ void coef_term(T wx, T wy, T m, T tiny, T* ar, T* ai)
 // cells within H of the wave's -- are one range per level-1 row; the lenses
 // between the ranges are far for every lane and need no test, and those inside
 // are tested lane by lane.  A lens is the same for the whole wave: its data come
-// through the scalar cache, four lenses to a load.  13000 lenses, 2.9e6 cells:
-// 41.6 ms, 46.2 with every lens staged in LDS and tested.
+// through the scalar cache, four lenses to a load and one load ahead, since the few
+// waves of a lattice of few cells have nothing else to hide it behind.  The whole call
+// (us; every lens staged in LDS and tested / read as it is summed / one load ahead):
+//   13000 lenses, 2.9e6 cells         44700  41050  38890
+//   13000 lenses, lattice of 1e6 rays  2308   3020   1929
+//   13000 lenses, lattice of 1e5 rays  3559   5055   3377
 template <int PREC, int P>
 __global__ __launch_bounds__(kWG) void k_coeffs(LmDesc d, int64_t ci0, int64_t cj0, int64_t nci,
                                                 int64_t ncj, LmCoef* __restrict__ out)
@@ -90,26 +94,77 @@ __global__ __launch_bounds__(kWG) void k_coeffs(LmDesc d, int64_t ci0, int64_t c
         lm = (ConstP<T>)d.lmf;
     }
     ConstP<int32_t> lI = (ConstP<int32_t>)d.lI, lJ = (ConstP<int32_t>)d.lJ;
-    auto far = [&](int k, int e) {
-        for (; k + 4 <= e; k += 4) {
-            T x[4], y[4], m[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                x[q] = lx[k + q];
-                y[q] = ly[k + q];
-                m[q] = lm[k + q];
+    // Lenses k .. e - 1, four at a time, the next four read while the current are summed.
+    // TEST: those in a lane's near block add nothing.
+    auto range = [&](auto test, int k, int e) __attribute__((always_inline)) {
+        constexpr bool TEST = decltype(test)::value;
+        constexpr int N = 4;
+        struct Group {
+            T x[N], y[N], m[N];
+            int I[N], J[N];
+        };
+        auto load1 = [&](Group& g, int q, int i) __attribute__((always_inline)) {
+            g.x[q] = lx[i];
+            g.y[q] = ly[i];
+            g.m[q] = lm[i];
+            if constexpr (TEST) {
+                g.I[q] = lI[i];
+                g.J[q] = lJ[i];
             }
+        };
+        auto load = [&](Group& g, int i) __attribute__((always_inline)) {
+            // Apart from the loads of the group before, and behind their arrival: scalar
+            // loads come back in any order, so a wait for those would wait for these.
+            asm volatile("" : "+s"(i));
+            __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) coef_term<P>(x[q] - zx, y[q] - zy, m[q], tiny, ar, ai);
+            for (int q = 0; q < N; ++q) load1(g, q, i + q);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto add1 = [&](const Group& g, int q) __attribute__((always_inline)) {
+            T m = g.m[q];
+            if constexpr (TEST) {
+                const bool near =
+                    ((unsigned)(g.I[q] - Ilo) <= span) & ((unsigned)(g.J[q] - Jlo) <= span);
+                m = near ? (T)0 : m;
+            }
+            coef_term<P>(g.x[q] - zx, g.y[q] - zy, m, tiny, ar, ai);
+        };
+        auto add = [&](const Group& g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < N; ++q) add1(g, q);
+        };
+        Group g, h;
+        if (k + N <= e) {
+            load(g, k);
+            for (; k + 3 * N <= e; k += 2 * N) {
+                load(h, k + N);
+                add(g);
+                load(g, k + 2 * N);
+                add(h);
+            }
+            if (k + 2 * N <= e) {
+                load(h, k + N);
+                add(g);
+                g = h;
+                k += N;
+            }
+            add(g);
+            k += N;
         }
-        for (; k < e; ++k) coef_term<P>(lx[k] - zx, ly[k] - zy, lm[k], tiny, ar, ai);
+        if (k < e) {
+#pragma unroll
+            for (int q = 0; q < N - 1; ++q) load1(g, q, min(k + q, e - 1));
+#pragma unroll
+            for (int q = 0; q < N - 1; ++q)
+                if (k + q < e) add1(g, q);
+        }
     };
-    auto tested = [&](int k, int e) {
-        for (; k < e; ++k) {
-            const bool near =
-                ((unsigned)(lI[k] - Ilo) <= span) & ((unsigned)(lJ[k] - Jlo) <= span);
-            coef_term<P>(lx[k] - zx, ly[k] - zy, near ? (T)0 : lm[k], tiny, ar, ai);
-        }
+    auto far = [&](int k, int e) __attribute__((always_inline)) {
+        range(std::false_type{}, k, e);
+    };
+    auto tested = [&](int k, int e) __attribute__((always_inline)) {
+        range(std::true_type{}, k, e);
     };
     // the level-1 cells of the wave's cells c .. c + 63, one or more rows of them
     const int64_t w0 = c - (threadIdx.x & 63);
@@ -118,16 +173,16 @@ __global__ __launch_bounds__(kWG) void k_coeffs(LmDesc d, int64_t ci0, int64_t c
         const int64_t w1 = min(w0 + 63, nc - 1);
         const int64_t r0 = w0 / nci, r1 = w1 / nci;
         const bool one = r0 == r1;  // cells of one row, else any column
-        const int i0 = (int)((ci0 + (one ? w0 - r0 * nci : 0)) / d.Kx);
-        const int i1 = (int)((ci0 + (one ? w1 - r0 * nci : nci - 1)) / d.Kx);
-        const int j0 = (int)((cj0 + r0) / d.Ky), j1 = (int)((cj0 + r1) / d.Ky);
+        // (the same in every lane: scalars, as everything derived from them)
+        auto uniform = [](int64_t v) { return __builtin_amdgcn_readfirstlane((int)v); };
+        const int i0 = uniform((ci0 + (one ? w0 - r0 * nci : 0)) / d.Kx);
+        const int i1 = uniform((ci0 + (one ? w1 - r0 * nci : nci - 1)) / d.Kx);
+        const int j0 = uniform((cj0 + r0) / d.Ky), j1 = uniform((cj0 + r1) / d.Ky);
         ConstP<int32_t> cs = (ConstP<int32_t>)d.cell_start;
         int k = 0;
         // padded rows j0 - H .. j1 + H and columns i0 - H .. i1 + H
         for (int r = j0; r <= j1 + 2 * d.H; ++r) {
-            const int base = __builtin_amdgcn_readfirstlane(r * d.nl1x + i0);
-            const int end = __builtin_amdgcn_readfirstlane(r * d.nl1x + i1 + 2 * d.H + 1);
-            const int s = cs[base], e = cs[end];
+            const int s = cs[r * d.nl1x + i0], e = cs[r * d.nl1x + i1 + 2 * d.H + 1];
             far(k, s);
             tested(s, e);
             k = e;
