@@ -81,8 +81,9 @@ __global__ __launch_bounds__(256) void k_peaks(const unsigned long long* __restr
 // Statistics of the listed rows over the pixel columns [col[0], col[nb]); column
 // p belongs to the last bin b with col[b] <= p.  True peaks are rare, so they
 // search their bin and add to hist (peaks[nb], heights[nb]) with global atomics.
-// The last workgroup to finish moves the sums to out, leaving hist and *done
-// zero as it found them.
+// With `done`, the last workgroup to finish moves the sums to out, leaving hist and
+// *done zero as it found them; without (more bins than one workgroup moves in a few
+// steps), k_peak_out does.
 __global__ __launch_bounds__(256) void k_peak_stats(const unsigned long long* __restrict__ counts,
                                                     int64_t nx, int64_t ny, LmTracks rows,
                                                     const int32_t* __restrict__ tracks, int64_t nt,
@@ -114,6 +115,7 @@ __global__ __launch_bounds__(256) void k_peak_stats(const unsigned long long* __
             __threadfence();
         }
     }
+    if (!done) return;
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();
@@ -126,6 +128,23 @@ __global__ __launch_bounds__(256) void k_peak_stats(const unsigned long long* __
     if (threadIdx.x == 0) atomicExch(done, 0u);
 }
 
+// The sums of k_peak_stats to out, hist left zero.
+__global__ __launch_bounds__(256) void k_peak_out(unsigned long long* __restrict__ hist, int n,
+                                                  unsigned long long* __restrict__ out)
+{
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i >= n) return;
+    out[i] = hist[i];
+    hist[i] = 0;
+}
+
+__global__ __launch_bounds__(256) void k_copy_i32(const int32_t* __restrict__ src, int64_t n,
+                                                  int32_t* __restrict__ dst)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
+
 }  // namespace
 
 int lm_launch_peak_stats(const unsigned long long* counts, int64_t nx, int64_t ny,
@@ -135,10 +154,34 @@ int lm_launch_peak_stats(const unsigned long long* counts, int64_t nx, int64_t n
                          void* stream)
 {
     if (nt <= 0) return 0;
-    const int64_t w = c1 > c0 ? c1 - c0 : 1;
-    const dim3 grid((unsigned)((w + 255) / 256), (unsigned)(nt < 65535 ? nt : 65535));
-    hipLaunchKernelGGL(k_peak_stats, grid, dim3(256), 0, (hipStream_t)stream, counts, nx, ny, rows,
-                       tracks, nt, (unsigned)(3 * k * k), bins, cols, c0, c1, nb, hist, done, out);
+    // At most 512 workgroups, each with every few-th row: their counts of `done` wait
+    // for one another (us a call, 300 rows of 4000 pixels: 132 with a workgroup to
+    // every 256 pixels, 42.5 so).  Up to kHandOff bins the last of them moves the
+    // sums (a launch less), more take a kernel of their own (us a call, 64 x 64 pixels,
+    // 20000 bins: 174 and 72).
+    constexpr int kHandOff = 1024;
+    const int64_t gx = ((c1 > c0 ? c1 - c0 : 1) + 255) / 256;
+    int64_t gy = gx < 512 ? 512 / gx : 1;
+    if (gy > nt) gy = nt;
+    const dim3 grid((unsigned)gx, (unsigned)gy);
+    hipStream_t s = (hipStream_t)stream;
+    const bool hand = nb <= kHandOff;
+    hipLaunchKernelGGL(k_peak_stats, grid, dim3(256), 0, s, counts, nx, ny, rows, tracks, nt,
+                       (unsigned)(3 * k * k), bins, cols, c0, c1, nb, hist, hand ? done : nullptr,
+                       out);
+    if (hand) return (int)hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return (int)e;
+    hipLaunchKernelGGL(k_peak_out, dim3((unsigned)((2 * nb + 255) / 256)), dim3(256), 0, s, hist,
+                       2 * nb, out);
+    return (int)hipGetLastError();
+}
+
+int lm_launch_copy_i32(const int32_t* src, int64_t n, int32_t* dst, void* stream)
+{
+    if (n <= 0) return 0;
+    hipLaunchKernelGGL(k_copy_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
+                       (hipStream_t)stream, src, n, dst);
     return (int)hipGetLastError();
 }
 

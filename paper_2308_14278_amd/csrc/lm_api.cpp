@@ -206,11 +206,16 @@ constexpr int kLanes = 8;
 constexpr size_t kLaneBytes = size_t(1) << 20;  // per buffer: 16 MiB a set
 constexpr size_t kStageBytes = 2 * kLanes * kLaneBytes;
 constexpr size_t kScratchBytes = size_t(8) << 20;  // a set's device scratch
-// ... of which the upper part holds histograms and a counter, zero between calls
+// ... of which the lower part takes a call's lists (rows of light curves, then first
+// columns of bins), or the precision probe, and the upper part holds histograms and
+// a counter, zero between calls
+constexpr size_t kRowsMax = size_t(1) << 20;
+constexpr size_t kColsOff = 4 * kRowsMax;
 constexpr int kHistBins = 1 << 16;
 constexpr size_t kHistOff = size_t(6) << 20;
 constexpr size_t kDoneOff = kHistOff + 16 * (size_t)kHistBins;
 static_assert(kDoneOff + 8 <= kScratchBytes, "histograms fit the scratch");
+static_assert(kColsOff + 4 * ((size_t)kHistBins + 1) <= kHistOff, "lists fit the scratch");
 
 struct Lane {
     unsigned long long* buf[2] = {nullptr, nullptr};
@@ -333,6 +338,26 @@ public:
 private:
     Stage* st_ = nullptr;
 };
+
+// A list of indices in device memory, ordered before the set's stream's later work:
+// through the set's pinned memory into its scratch (both at byte `off`, which hold up
+// to `room` of them), else by a plain copy into `own`.
+lm_status put_list(const StageUse& sg, const int32_t* list, int64_t n, size_t off, size_t room,
+                   DevBuf& own, const int32_t*& dev)
+{
+    if (sg && (size_t)n <= room) {
+        int32_t* pin = reinterpret_cast<int32_t*>(reinterpret_cast<unsigned char*>(sg->mem) + off);
+        int32_t* d = reinterpret_cast<int32_t*>(sg->dev() + off);
+        std::copy(list, list + n, pin);
+        LAUNCH_TRY(lm_launch_copy_i32(pin, n, d, sg->lane[0].s));
+        dev = d;
+        return LM_OK;
+    }
+    if (own.ensure((size_t)n * 4)) return fail(LM_ENOMEM, "cannot allocate");
+    HIP_TRY(hipMemcpy(own.p, list, (size_t)n * 4, hipMemcpyHostToDevice));
+    dev = own.as<int32_t>();
+    return LM_OK;
+}
 
 // Counts the live maps; the kept sets go with the last one.
 struct MapCount {
@@ -1599,9 +1624,8 @@ lm_status lm_find_peaks(lm_map* m, const int32_t* tracks, int32_t n_tracks, int3
     if (n_tracks <= LM_ARG_TRACKS) {
         std::copy(tracks, tracks + n_tracks, rows.row);
     } else {
-        if (dt.ensure((size_t)n_tracks * 4)) return fail(LM_ENOMEM, "cannot allocate");
-        HIP_TRY(hipMemcpy(dt.p, tracks, (size_t)n_tracks * 4, hipMemcpyHostToDevice));
-        dev_tracks = dt.as<int32_t>();
+        st = put_list(sg, tracks, n_tracks, 0, kRowsMax, dt, dev_tracks);
+        if (st) return st;
     }
     for (int64_t t0 = 0; t0 < n_tracks; t0 += per) {
         const int64_t c = std::min<int64_t>(per, n_tracks - t0);
@@ -1626,8 +1650,8 @@ namespace {
 // and the count of finished workgroups, zero, and where the kernel writes the
 // sums: pinned memory, or device memory that is copied.
 struct PeakScratch {
-    int32_t* tracks;
-    int32_t* cols;
+    const int32_t* tracks;
+    const int32_t* cols;
     unsigned long long* hist;
     unsigned* done;
     unsigned long long* out;
@@ -1660,11 +1684,23 @@ lm_status peak_stats_check(lm_map* m, const int32_t* tracks, int32_t n_tracks, i
 // in FP64 in that order, do not decrease with p.
 void bin_columns(const lm_geometry& g, const double* edges, int32_t n_bins, int32_t* col)
 {
-    for (int32_t b = 0; b <= n_bins; ++b) {
+    auto centre = [&g](int64_t p) { return g.src_x0 + ((double)p + 0.5) * g.src_dx; };
+    if (n_bins >= g.src_nx) {  // the bin of every column
+        int32_t* b = col;
+        for (int64_t p = 0; p < g.src_nx; ++p) {
+            int32_t* e = col + (std::upper_bound(edges + (b - col), edges + n_bins + 1, centre(p)) -
+                                edges);
+            std::fill(b, e, (int32_t)p);
+            b = e;
+        }
+        std::fill(b, col + n_bins + 1, (int32_t)g.src_nx);
+        return;
+    }
+    for (int32_t b = 0; b <= n_bins; ++b) {  // the column of every edge
         int64_t lo = b > 0 ? col[b - 1] : 0, hi = g.src_nx;
         while (lo < hi) {
             const int64_t p = lo + (hi - lo) / 2;
-            if (g.src_x0 + ((double)p + 0.5) * g.src_dx >= edges[b])
+            if (centre(p) >= edges[b])
                 hi = p;
             else
                 lo = p + 1;
@@ -1673,22 +1709,16 @@ void bin_columns(const lm_geometry& g, const double* edges, int32_t n_bins, int3
     }
 }
 
-// The statistics proper, on buffers the caller provides; col as bin_columns.
+// The statistics proper, on buffers the caller provides (who has waited for the
+// device); col as bin_columns.
 lm_status peak_stats_run(lm_map* m, const int32_t* tracks, int32_t n_tracks, int32_t k,
                          const int32_t* col, int32_t n_bins, uint64_t* peaks, uint64_t* heights,
                          const PeakScratch& d)
 {
-    HIP_TRY(hipDeviceSynchronize());
     LmTracks rows{};
     LmBins bins{};
-    if (d.tracks)
-        HIP_TRY(hipMemcpy(d.tracks, tracks, (size_t)n_tracks * 4, hipMemcpyHostToDevice));
-    else
-        std::copy(tracks, tracks + n_tracks, rows.row);
-    if (d.cols)
-        HIP_TRY(hipMemcpy(d.cols, col, (size_t)(n_bins + 1) * 4, hipMemcpyHostToDevice));
-    else
-        std::copy(col, col + n_bins + 1, bins.col);
+    if (!d.tracks) std::copy(tracks, tracks + n_tracks, rows.row);
+    if (!d.cols) std::copy(col, col + n_bins + 1, bins.col);
     LAUNCH_TRY(lm_launch_peak_stats(reinterpret_cast<const unsigned long long*>(m->counts),
                                     m->g.src_nx, m->g.src_ny, rows, d.tracks, n_tracks, k, bins,
                                     d.cols, col[0], col[n_bins], n_bins, d.hist, d.done, d.out,
@@ -1740,12 +1770,18 @@ lm_status lm_peak_stats(lm_map* m, const int32_t* tracks, int32_t n_tracks, int3
     if (st) return st;
     if (n_tracks == 0) return ok();
     static_assert((size_t)kHistBins * 16 <= kStageBytes, "the sums fit the pinned memory");
+    HIP_TRY(hipDeviceSynchronize());
     StageUse sg(m->device);
     DevBuf dt, dc, dh;
-    if ((n_tracks > LM_ARG_TRACKS && dt.ensure((size_t)n_tracks * 4)) ||
-        (n_bins > LM_ARG_BINS && dc.ensure((size_t)(n_bins + 1) * 4)))
-        return fail(LM_ENOMEM, "cannot allocate");
-    PeakScratch d{dt.as<int32_t>(), dc.as<int32_t>(), nullptr, nullptr, nullptr, false, nullptr};
+    PeakScratch d{};
+    if (n_tracks > LM_ARG_TRACKS) {
+        st = put_list(sg, tracks, n_tracks, 0, kRowsMax, dt, d.tracks);
+        if (st) return st;
+    }
+    if (n_bins > LM_ARG_BINS) {
+        st = put_list(sg, col.data(), (int64_t)n_bins + 1, kColsOff, (size_t)kHistBins + 1, dc, d.cols);
+        if (st) return st;
+    }
     if (sg) {
         d.hist = reinterpret_cast<unsigned long long*>(sg->dev() + kHistOff);
         d.done = reinterpret_cast<unsigned*>(sg->dev() + kDoneOff);
@@ -1787,13 +1823,17 @@ lm_status lm_peak_stats_noalloc(lm_map* m, const int32_t* tracks, int32_t n_trac
     void* base = nullptr;
     LAUNCH_TRY(lm_scratch_address(&base));
     unsigned char* s = static_cast<unsigned char*>(base);
-    const PeakScratch d{reinterpret_cast<int32_t*>(s),
-                        reinterpret_cast<int32_t*>(s + LM_SCRATCH_OFF_BINS),
+    const PeakScratch d{reinterpret_cast<const int32_t*>(s),
+                        reinterpret_cast<const int32_t*>(s + LM_SCRATCH_OFF_BINS),
                         reinterpret_cast<unsigned long long*>(s + LM_SCRATCH_OFF_HIST),
                         reinterpret_cast<unsigned*>(s + LM_SCRATCH_OFF_DONE),
                         reinterpret_cast<unsigned long long*>(s + LM_SCRATCH_OFF_OUT),
                         false,
                         nullptr};
+    HIP_TRY(hipDeviceSynchronize());
+    HIP_TRY(hipMemcpy(s, tracks, (size_t)n_tracks * 4, hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(s + LM_SCRATCH_OFF_BINS, col.data(), (size_t)(n_bins + 1) * 4,
+                      hipMemcpyHostToDevice));
     // the histograms are cleared at the start of each call
     LAUNCH_TRY(lm_launch_fill_u64(d.hist, (LM_SCRATCH_OFF_OUT - LM_SCRATCH_OFF_HIST) / 8, 0ull,
                                   nullptr));

@@ -283,6 +283,8 @@ int lm_launch_peak_stats(const unsigned long long* counts, int64_t nx, int64_t n
                          const LmBins& bins, const int32_t* cols, int c0, int c1, int nb,
                          unsigned long long* hist, unsigned* done, unsigned long long* out,
                          void* stream);
+// n indices from pinned to device memory
+int lm_launch_copy_i32(const int32_t* src, int64_t n, int32_t* dst, void* stream);
 int lm_shoot_occupancy(int scheme, int precision, int terms, int rays_per_lane, int layout,
                        int* wg_per_cu);
 // Device address of the current device's scratch array (resolved once per
