@@ -174,10 +174,16 @@ typedef struct lm_batch lm_batch;
 /* Create a map with the given geometry on the current HIP device (Sec. 3.2: the
  * ray lattice and its cells; Sec. 3.2.3: one count per source pixel).  Counts
  * start at zero; the macro model is kappa = gamma = kappa_star = 0 and there
- * are no lenses until set.  The map owns its device buffers.  LM_EINVAL for an invalid geometry (non-positive
- * sizes, coarse not a positive multiple of 64, more than 2^31 rays per
- * workgroup tile, P outside 1..LM_MAX_TERMS, src_nx or src_ny above 2^30,
- * src_nx*src_ny >= 2^40). */
+ * are no lenses until set.  The map owns its device buffers.  LM_EINVAL for an
+ * invalid geometry (non-positive sizes, coarse not a positive multiple of 64,
+ * more than 2^31 rays per workgroup tile, P outside 1..LM_MAX_TERMS, src_nx or
+ * src_ny above 2^30, src_nx*src_ny >= 2^40).
+ *
+ * Calls that move data between host and device do so through staging sets of 16
+ * MiB of pinned host memory, 8 MiB of device memory and a few streams.  A call has
+ * a set to itself; up to four are kept on each device between calls while any map
+ * of the device lives.  A call that cannot have one copies plainly.  Reads of 4
+ * MiB and more run up to seven threads of their own until they return. */
 lm_status lm_create(const lm_geometry* g, lm_map** out);
 
 /* Release every resource of the map (NULL is ignored).  Waits for the map's

@@ -13,7 +13,6 @@
 #include <fstream>
 #include <map>
 #include <memory>
-#include <mutex>
 #include <new>
 #include <numeric>
 #include <sstream>
@@ -24,6 +23,7 @@
 
 #include "../../include/lensmap.h"
 #include "lm_internal.h"
+#include "lm_pool.h"
 
 namespace {
 
@@ -276,38 +276,16 @@ struct Stage {
     }
 };
 
-// Sets not in use: at most kStagesKept of them, kept while any map lives and
-// freed with the last one.  A call takes a set for itself, so calls on several
-// threads never share one.
-constexpr size_t kStagesKept = 2;
-
-struct StagePool {
-    std::mutex mu;
-    Stage* kept[kStagesKept] = {nullptr, nullptr};
-    int64_t maps = 0;
-};
-
-StagePool& stage_pool()
-{
-    static StagePool* p = new StagePool;  // never destroyed: the HIP runtime may go first
-    return *p;
-}
+// Sets not in use, up to kStagesKept on each device, freed with its last map.
+constexpr int kStagesKept = 4;
+DevicePool<Stage, kStagesKept, LM_MAX_DEVICES> g_stages;
 
 // A set for the current call on `device`, returned to the pool at its end.
 class StageUse {
 public:
-    explicit StageUse(int device)
+    explicit StageUse(int device) : st_(g_stages.take(device))
     {
-        StagePool& P = stage_pool();
-        {
-            std::lock_guard<std::mutex> lock(P.mu);
-            for (Stage*& k : P.kept)
-                if (k && k->device == device) {
-                    st_ = k;
-                    k = nullptr;
-                    return;
-                }
-        }
+        if (st_) return;
         std::unique_ptr<Stage> s(new (std::nothrow) Stage);
         if (s && s->init(device) == hipSuccess) {
             st_ = s.release();
@@ -317,18 +295,7 @@ public:
     }
     ~StageUse()
     {
-        if (!st_) return;
-        StagePool& P = stage_pool();
-        {
-            std::lock_guard<std::mutex> lock(P.mu);
-            if (P.maps > 0)
-                for (Stage*& k : P.kept)
-                    if (!k) {
-                        k = st_;
-                        return;
-                    }
-        }
-        delete st_;
+        if (st_ && !g_stages.keep(st_->device, st_)) delete st_;
     }
     StageUse(const StageUse&) = delete;
     StageUse& operator=(const StageUse&) = delete;
@@ -359,24 +326,18 @@ lm_status put_list(const StageUse& sg, const int32_t* list, int64_t n, size_t of
     return LM_OK;
 }
 
-// Counts the live maps; the kept sets go with the last one.
+// A map's share in the staging sets of its device.
 struct MapCount {
-    MapCount()
+    int device = -1;
+    void begin(int dev)
     {
-        StagePool& P = stage_pool();
-        std::lock_guard<std::mutex> lock(P.mu);
-        ++P.maps;
+        device = dev;
+        g_stages.enter(dev);
     }
+    MapCount() = default;
     ~MapCount()
     {
-        StagePool& P = stage_pool();
-        Stage* drop[kStagesKept] = {nullptr, nullptr};
-        {
-            std::lock_guard<std::mutex> lock(P.mu);
-            if (--P.maps == 0)
-                for (size_t k = 0; k < kStagesKept; ++k) std::swap(drop[k], P.kept[k]);
-        }
-        for (Stage* s : drop) delete s;
+        if (device >= 0) g_stages.leave(device);
     }
     MapCount(const MapCount&) = delete;
     MapCount& operator=(const MapCount&) = delete;
@@ -947,6 +908,7 @@ lm_status lm_create(const lm_geometry* g, lm_map** out)
     if (!m) return fail(LM_ENOMEM, "out of host memory");
     m->g = *g;
     HIP_TRY(hipGetDevice(&m->device));
+    m->counted.begin(m->device);
     m->cus = device_cus(m->device);
     m->ncx = ceil_div(g->ray_nx, g->coarse);
     m->ncy = ceil_div(g->ray_ny, g->coarse);
