@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <fstream>
 #include <map>
 #include <memory>
@@ -17,7 +18,6 @@
 #include <numeric>
 #include <sstream>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -245,7 +245,7 @@ struct Stage {
         if (e != hipSuccess) return e;
         mem = static_cast<unsigned long long*>(p);
         e = scratch.ensure(kScratchBytes);
-        if (e == hipSuccess) e = open(1);
+        if (e == hipSuccess && open(1) < 1) e = hipErrorOutOfMemory;
         return e != hipSuccess ? e : clear_hist();
     }
     unsigned char* dev() const { return scratch.as<unsigned char>(); }
@@ -256,23 +256,28 @@ struct Stage {
             0ull, lane[0].s);
         return e != hipSuccess ? e : hipStreamSynchronize(lane[0].s);
     }
-    // Makes the first n lanes ready: each stream makes a wait for the device
-    // longer, so only large reads open more than one.
-    hipError_t open(int n)
+    // Makes the first n lanes ready, or as many as streams and events can be had for:
+    // each stream makes a wait for the device longer, so only large reads open more
+    // than one.
+    int open(int n)
     {
         for (int k = 0; k < n; ++k) {
             Lane& l = lane[k];
             if (l.s) continue;
             for (int b = 0; b < 2; ++b) {
                 l.buf[b] = mem + (2 * k + b) * (kLaneBytes / 8);
-                if (l.ev[b]) continue;
-                const hipError_t e = hipEventCreateWithFlags(&l.ev[b], hipEventDisableTiming);
-                if (e != hipSuccess) return e;
+                if (!l.ev[b] &&
+                    hipEventCreateWithFlags(&l.ev[b], hipEventDisableTiming) != hipSuccess)
+                    l.ev[b] = nullptr;
             }
-            const hipError_t e = hipStreamCreateWithFlags(&l.s, hipStreamNonBlocking);
-            if (e != hipSuccess) return e;
+            if (!l.ev[0] || !l.ev[1] ||
+                hipStreamCreateWithFlags(&l.s, hipStreamNonBlocking) != hipSuccess) {
+                l.s = nullptr;
+                (void)hipGetLastError();
+                return k;
+            }
         }
-        return hipSuccess;
+        return n;
     }
 };
 
@@ -1223,10 +1228,9 @@ hipError_t read_lane(const ReadJob& r, Lane& l, int64_t k, int64_t step)
 hipError_t read_job(const ReadJob& r, Stage& st)
 {
     const int64_t nk = ceil_div(r.n, (int64_t)(kLaneBytes / 8));
-    const int nt = (int)std::min<int64_t>(kLanes, nk / 2);
+    int nt = (int)std::min<int64_t>(kLanes, nk / 2);
+    if (nt >= 2) nt = st.open(nt);
     if (nt < 2) return read_lane(r, st.lane[0], 0, 1);
-    const hipError_t opened = st.open(nt);
-    if (opened != hipSuccess) return opened;
     hipError_t err[kLanes];
     std::thread th[kLanes];
     int started = 1;  // lane 0 runs here
@@ -1237,8 +1241,8 @@ hipError_t read_job(const ReadJob& r, Stage& st)
                 err[k] = hipSetDevice(st.device);
                 if (err[k] == hipSuccess) err[k] = read_lane(r, st.lane[k], k, nt);
             });
-        } catch (const std::system_error&) {
-            break;  // no more threads: the rest runs here
+        } catch (const std::exception&) {
+            break;  // no more threads, or no memory for one: the rest runs here
         }
     }
     err[0] = read_lane(r, st.lane[0], 0, nt);
