@@ -1170,7 +1170,8 @@ lm_status lm_shoot(lm_map* m, int64_t i0, int64_t j0, int64_t ni, int64_t nj, vo
     e.nr = sp.nr;
     LmDesc d = make_desc(m, i0, j0, i0 + ni, j0 + nj, e);
     if (d.ntiles > 0x7fffffffLL) return fail(LM_EUNSUPPORTED, "too many workgroup tiles");
-    LAUNCH_TRY(lm_launch_shoot_map(d, m->g.scheme, m->prec, m->g.taylor_terms, e.nr, s));
+    const int terms = form == 0 ? lm_direct_terms(m->nlens) : m->g.taylor_terms;
+    LAUNCH_TRY(lm_launch_shoot_map(d, m->g.scheme, m->prec, terms, e.nr, s));
     m->n_shot += (uint64_t)ni * (uint64_t)nj;
     m->has_counts = true;
     m->last = s;
@@ -1888,6 +1889,7 @@ struct BatchGroup {
     DevBuf offs, order;
     int64_t total = 0;  // tiles in the queue
     int grid = 0;
+    int nr = 16, terms = 4;  // rays per lane and terms of the kernel
 };
 
 struct lm_batch {
@@ -1896,7 +1898,6 @@ struct lm_batch {
     std::vector<uint64_t> gens; // each map's generation when the graphs were built
     int scheme = 0, terms = 4, device = 0;
     int rays_per_lane = 16, g_scale = 1, wg_per_cu = 0;
-    int nr = 16;  // rays per lane of the built tables' launches (rays_per_lane, or lm_direct_nr)
     int layout = 0;             // LDS layout of the LM_PREC_MIXED group (others use 0)
     DevBuf descs;               // one LmDesc per map
     BatchGroup grp[kGroups];    // indexed by precision
@@ -1944,9 +1945,6 @@ lm_status batch_build(lm_batch* b, const std::vector<int64_t>& work)
         lm_status st = resolve_precision(m, b->cap);
         if (st) return st;
     }
-    b->nr = b->rays_per_lane;
-    if (b->scheme == LM_SCHEME_DIRECT)
-        for (lm_map* m : b->maps) b->nr = lm_direct_nr(b->nr, m->nlens);
     std::vector<LmDesc> ds(n);
     std::vector<double> cost(n);
     for (int k = 0; k < n; ++k) {
@@ -1957,7 +1955,7 @@ lm_status batch_build(lm_batch* b, const std::vector<int64_t>& work)
         rect_cells(m->g.coarse, own[0], own[1], own[2], own[3], cx, cy);
         const Exec e = choose_exec(
             m, cx, cy, b->g_scale,
-            window_bins(m->g.scheme, m->prec, group_layout(b, m->prec), b->nr));
+            window_bins(m->g.scheme, m->prec, group_layout(b, m->prec), b->rays_per_lane));
         ds[k] = make_desc(m, r[0], r[1], r[0] + r[2], r[1] + r[3], e);
         if (r[2] == 0 || r[3] == 0) ds[k].ntiles = 0;
         if (ds[k].ntiles > 0x7fffffffLL)
@@ -1988,8 +1986,15 @@ lm_status batch_build(lm_batch* b, const std::vector<int64_t>& work)
         HIP_TRY(hipMemcpy(G.offs.p, offs.data(), (G.nmaps + 1) * 8, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(G.order.p, order.data(), G.nmaps * 4, hipMemcpyHostToDevice));
         int occ = 0;
-        LAUNCH_TRY(
-            lm_shoot_occupancy(b->scheme, pr, b->terms, b->nr, group_layout(b, pr), &occ));
+        G.nr = b->rays_per_lane;
+        G.terms = b->terms;
+        if (b->scheme == LM_SCHEME_DIRECT) {
+            for (int k : order) G.terms = std::max(G.terms, lm_direct_terms(b->maps[k]->nlens));
+            // (16 rays per lane and long lists: two workgroups to a CU)
+            if (G.terms == kLongList && G.total > 2 * (int64_t)device_cus(b->device))
+                G.nr = std::min(G.nr, 8);
+        }
+        LAUNCH_TRY(lm_shoot_occupancy(b->scheme, pr, G.terms, G.nr, group_layout(b, pr), &occ));
         if (occ <= 0) occ = 1;
         const int wg = b->wg_per_cu > 0 ? std::min(b->wg_per_cu, occ) : occ;
         // no more workgroups than tiles: one that finds none still clears its window and
@@ -2021,7 +2026,7 @@ lm_status batch_enqueue(lm_batch* b, hipStream_t s, bool with_coeffs, bool pre =
             LAUNCH_TRY(lm_launch_shoot_batch(b->descs.as<LmDesc>(), G.offs.as<int64_t>(),
                                              G.order.as<int32_t>(), G.nmaps,
                                              b->queue.as<unsigned long long>() + pr, b->scheme,
-                                             pr, b->terms, b->nr, group_layout(b, pr), G.grid, s));
+                                             pr, G.terms, G.nr, group_layout(b, pr), G.grid, s));
         }
     return LM_OK;
 }

@@ -32,15 +32,17 @@ struct Cap {
     static constexpr int value = SCHEME == 0 ? LM_LENS_CAP : kLayNear[LAY];
 };
 
-// Direct sum with 16 rays per lane: lists of one block only, so that no instance
-// holds the compensation of several blocks beside 16 rays: that spilled 107 registers
-// to scratch memory, whose set-up alone cost a launch of few lenses 2 us (us, one lens
-// 1400 x 1400 rays: 24.3 and 18.0; 200 lenses, 2000 x 2000: 142 and 131).  Longer lists
-// run 8 (lm_direct_nr), as fast as 16 with the spills (1000 lenses, 4000 x 4000: 2449
-// and 2406 us), in plain FP32 4% slower.
-template <int SCHEME, int NR>
+// The direct scheme has no Taylor terms: its kernels are built for P = 1, lists of one
+// block of lenses, and P = 2 (kLongList), lists of several, whose compensation is held
+// beside the rays.  One kernel for both spilled 107 registers to scratch memory at 16
+// rays per lane, whose set-up alone cost a launch of few lenses 2 us (us, one lens, 1400
+// x 1400 rays: 24.3 and 18.0; 200 lenses, 2000 x 2000: 142 and 131).  Long lists at 16
+// rays per lane take the registers of two waves per SIMD, for launches that do not fill
+// more; others run 8 (us, 1000 lenses, 4000 x 4000 rays: 2398, with the spills 2456; a
+// batch of one 2000 x 2000 map in 49 tiles, 400 lenses: 2857 at 16, 3482 at 8).
+template <int SCHEME, int P>
 struct OneBlock {
-    static constexpr bool value = SCHEME == 0 && NR == 16;
+    static constexpr bool value = SCHEME == 0 && P != kLongList;
 };
 
 // Arithmetic of the ray-lens pairs: FP32 (rebased or plain global) or FP64
@@ -67,9 +69,10 @@ struct UseTab {
 // Waves per SIMD the shooting kernels must keep: the FP32 paths are issue-bound
 // and need 4 (at most 128 VGPRs with 256-thread workgroups, 4 per CU); the FP64 sums fit 3 (168 VGPRs; at the 220 they took without the hint
 // two waves ran).
-template <int SCHEME, int PREC>
+template <int SCHEME, int PREC, int NR, int P>
 struct MinWaves {
-    static constexpr int value = SCHEME == 1 && PREC == 2 ? 3 : 4;
+    static constexpr int value = SCHEME == 1 ? (PREC == 2 ? 3 : 4)
+                                 : P == kLongList && NR == 16 ? 2 : 4;
 };
 
 __device__ __forceinline__ void wave_sync_lds()
@@ -1142,7 +1145,7 @@ __device__ __forceinline__ void table_start(const typename Prec<PREC>::T* tb,
 // Columns [c_lo, c_hi) of cell ci are computed (c_lo even, so columns 2m and
 // 2m + 1 share a group); rays of columns >= c_beg are counted.  LAY: the LDS
 // layout (near-list block, table block).
-template <int SCHEME, int PREC, int NR, int P, bool FOLD, int LAY>
+template <int SCHEME, int PREC, int NR, int PK, bool FOLD, int LAY>
 __device__ __forceinline__ void process_unit(const LmDesc& d, int64_t ci, int64_t cj, int64_t c_lo, int64_t c_beg,
                              int64_t c_hi, int64_t j, bool row_ok, const Win& w,
                              unsigned* win, typename Prec<PREC>::L* lb,
@@ -1150,6 +1153,7 @@ __device__ __forceinline__ void process_unit(const LmDesc& d, int64_t ci, int64_
 {
     using T = typename Prec<PREC>::T;
     constexpr bool CENT = PREC == kPrecCentred;
+    constexpr int P = SCHEME == 0 ? 1 : PK;  // Taylor terms
     const int R = d.R;
     const Hot h = make_hot(d);
     const double zcx = cell_cx(d, ci), zcy = cell_cy(d, cj);
@@ -1236,19 +1240,17 @@ __device__ __forceinline__ void process_unit(const LmDesc& d, int64_t ci, int64_
         // direct sum over one block of lenses: the first step of the compensated sum,
         // whose compensation is not needed; the rays start after their lenses, so that
         // neither takes registers in the lens loop
-        const bool one = SCHEME == 0 && (OneBlock<SCHEME, NR>::value || nblk <= 1);
-        if constexpr (SCHEME == 0) {
-            if (one) {
-                T bx[NR], by[NR];
+        constexpr bool one = OneBlock<SCHEME, PK>::value;
+        if constexpr (one) {
+            T bx[NR], by[NR];
 #pragma unroll
-                for (int c = 0; c < NR; ++c) bx[c] = by[c] = 0;
-                direct_loop<NR>(lb, count, px, py, bx, by);
-                start();
+            for (int c = 0; c < NR; ++c) bx[c] = by[c] = 0;
+            direct_loop<NR>(lb, count, px, py, bx, by);
+            start();
 #pragma unroll
-                for (int c = 0; c < NR; ++c) {
-                    ax[c] += bx[c];
-                    ay[c] += by[c];
-                }
+            for (int c = 0; c < NR; ++c) {
+                ax[c] += bx[c];
+                ay[c] += by[c];
             }
         }
         if (!POW && !one) start();
@@ -1454,7 +1456,7 @@ __device__ __forceinline__ void flush_window(const LmDesc& d, unsigned* win, int
 
 template <int SCHEME, int PREC, int NR, int P>
 __global__ __launch_bounds__(kWG)
-__attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot_map(LmDesc arg)
+__attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC, NR, P>::value))) void k_shoot_map(LmDesc arg)
 {
     // The interpolated scheme reads the descriptor, the kernel's only argument, where
     // it is used: as an argument by name its fields are loaded at the start and kept,
@@ -1486,7 +1488,7 @@ __attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot
 
 template <int SCHEME, int PREC, int NR, int P, int LAY>
 __global__ __launch_bounds__(kWG)
-__attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC>::value))) void k_shoot_batch(const LmDesc* __restrict__ descs,
+__attribute__((amdgpu_waves_per_eu(MinWaves<SCHEME, PREC, NR, P>::value))) void k_shoot_batch(const LmDesc* __restrict__ descs,
                                                      const int64_t* __restrict__ offs,
                                                      const int32_t* __restrict__ order, int nmaps,
                                                      unsigned long long* queue)
@@ -1815,7 +1817,7 @@ int dispatch_layout(int layout, F& f)
 }
 
 // Visit the instantiation for runtime (scheme, precision, NR, P).  The direct
-// scheme has no Taylor terms and is instantiated with P = 1 only.
+// scheme has no Taylor terms: P = 1, and for the shooting kernels kLongList.
 template <int S, int PR, int NR, class F>
 int dispatch_p(int terms, F& f)
 {
@@ -1835,13 +1837,22 @@ int dispatch_p(int terms, F& f)
     }
 }
 
+template <int S, int PR, int NR, class F>
+int dispatch_shoot(int terms, F& f)
+{
+    if constexpr (S == 0) {
+        if (terms == kLongList) return f.template go<S, PR, NR, kLongList>();
+    }
+    return dispatch_p<S, PR, NR>(terms, f);
+}
+
 template <int S, int PR, class F>
 int dispatch_nr(int nr, int terms, F& f)
 {
     switch (nr) {
-    case 4: return dispatch_p<S, PR, 4>(terms, f);
-    case 8: return dispatch_p<S, PR, 8>(terms, f);
-    case 16: return dispatch_p<S, PR, 16>(terms, f);
+    case 4: return dispatch_shoot<S, PR, 4>(terms, f);
+    case 8: return dispatch_shoot<S, PR, 8>(terms, f);
+    case 16: return dispatch_shoot<S, PR, 16>(terms, f);
     default: return (int)hipErrorInvalidValue;
     }
 }

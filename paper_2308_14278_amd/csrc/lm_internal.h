@@ -10,6 +10,10 @@
 // deflection change from the level-2 cell centre, whose near-lens deflection
 // is taken in FP64 (n0 below).
 constexpr int kPrecCentred = 4;
+// The `terms` the direct scheme's shooting kernels are asked for with: 1, or for lists
+// of more than one block of lenses this.
+constexpr int kLongList = 2;
+constexpr int lm_direct_terms(int64_t nlens) { return nlens > LM_LENS_CAP ? kLongList : 1; }
 
 // LDS layouts of the interpolated-scheme shooting kernels, the tuner's third
 // axis besides rays per lane and tile size: lenses per LDS table block (the
@@ -122,10 +126,6 @@ struct LmDesc {
     int32_t split;
 };
 
-// Rays per lane of a direct sum over nlens lenses when nr are asked for: its kernels
-// for 16 take one block of lenses.
-constexpr int lm_direct_nr(int nr, int64_t nlens) { return nlens > LM_LENS_CAP && nr > 8 ? 8 : nr; }
-
 // How a launch for one map shares its tiles out: workgroups to a tile, columns per
 // chunk of a cell, rays per lane.
 struct LmSplit {
@@ -177,10 +177,13 @@ inline LmSplit lm_split(int form, int R, int ncc, int cw, int G, int64_t tiles, 
         const double k = G > 1 ? 4.0
                                : (double)up(tiles * up(chunks, ncc), cus) *
                                      (double)(units < LM_WAVES ? units : LM_WAVES) / LM_WAVES;
-        for (int q = form == 0 && longest > LM_LENS_CAP; q < 3; ++q) {
-            const int nr = 16 >> q;  // (lm_direct_nr)
+        for (int q = 0; q < 3; ++q) {
+            const int nr = 16 >> q;
             const double alone = lat[form][q] * (longest + col);
-            const double shared = k * issue[form][q] * (list + col);
+            // (long direct lists run two waves per SIMD at 16 rays per lane)
+            const double each =
+                q == 0 && form == 0 && longest > LM_LENS_CAP ? 165.0 : issue[form][q];
+            const double shared = k * each * (list + col);
             const double t =
                 (double)(up(units, LM_WAVES) * up(ncol, nr)) * (alone > shared ? alone : shared) +
                 25.0 * (double)(s * tiles);

@@ -692,8 +692,7 @@ int lm_launch_shoot_map(const LmDesc& d, int scheme, int precision, int terms, i
                         void* stream)
 {
     if (d.ntiles <= 0) return 0;
-    if (scheme == 0 && rays_per_lane != lm_direct_nr(rays_per_lane, d.nlens))
-        return (int)hipErrorInvalidValue;
+    if (scheme == 0 && terms != lm_direct_terms(d.nlens)) return (int)hipErrorInvalidValue;
 #define X(S, PR)                                                                            \
     if (scheme == S && precision == PR)                                                     \
         return LM_INST_CAT(lm_inst_shoot_map, S, PR)(d, rays_per_lane, terms, stream);

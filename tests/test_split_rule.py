@@ -95,9 +95,8 @@ def test_narrow_rectangles_run_fewer_rays_per_lane(rule, form, ni, nr):
     assert rule(form, 320, ni, 700 * 320, 0) == (1, 80, nr)
 
 
-@pytest.mark.parametrize("lens,most", [(256, 16), (257, 8), (100000, 8)])
-def test_long_direct_lists_run_eight_rays_per_lane(rule, lens, most):
-    """The direct kernels for 16 rays per lane take one block of lenses."""
-    got = [rule(DIRECT, R, ni, nj, lens, G=G)[2] for R in (64, 128, 512) for G in (1, 4)
-           for ni, nj in ((1, 1), (9, 700), (1000, 1000), (9000, 9000), (100 * R, 100 * R))]
-    assert max(got) == most
+def test_long_direct_lists(rule):
+    """Lists of several blocks of lenses run 16 rays per lane two waves to a SIMD: full
+    launches take 8."""
+    assert rule(DIRECT, 64, 9000, 9000, 256)[2] == 16
+    assert rule(DIRECT, 64, 9000, 9000, 257)[2] == 8
