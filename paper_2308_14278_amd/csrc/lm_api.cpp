@@ -1287,6 +1287,16 @@ lm_status read_map(lm_map* m, int64_t p0, int64_t q0, int64_t np, int64_t nq, bo
     }
     Lane& l = st->lane[0];
     const int64_t small = (int64_t)(kLaneBytes / 8) - 1;
+    // Magnifications of 16 to 64 KiB by the runtime's copy, converted here: above 16 KiB
+    // it takes 8.6 us (below 12.5), a launch and its wait 12, and an entry's conversion
+    // 0.5 ns here (us a call on an idle device, launch and copy: 3000 entries 14.7 and
+    // 11.7, 6000 15.3 and 13.3; at 8192 they meet)
+    if (mu && !n_out && r.whole && r.n > 2048 && r.n <= 8192) {
+        HIP_TRY(hipMemcpy(l.buf[0], m->counts, (size_t)r.n * 8, hipMemcpyDeviceToHost));
+        double* v = static_cast<double*>(dst);
+        for (int64_t k = 0; k < r.n; ++k) v[k] = (double)l.buf[0][k] * r.factor;
+        return ok();
+    }
     if (r.n <= small) {  // the window and n_out in one launch
         LAUNCH_TRY(lm_launch_read_back(r.map, r.snx, p0, q0, np, r.whole, mu, 0, r.n, r.factor,
                                        l.buf[0], m->n_out.as<unsigned long long>(), l.s));

@@ -67,8 +67,9 @@ struct UseTab {
 };
 
 // Waves per SIMD the shooting kernels must keep: the FP32 paths are issue-bound
-// and need 4 (at most 128 VGPRs with 256-thread workgroups, 4 per CU); the FP64 sums fit 3 (168 VGPRs; at the 220 they took without the hint
-// two waves ran).
+// and need 4 (at most 128 VGPRs with 256-thread workgroups, 4 per CU), but for long
+// direct lists at 16 rays per lane (OneBlock); the FP64 sums fit 3 (168 VGPRs; at the
+// 220 they took without the hint two waves ran).
 template <int SCHEME, int PREC, int NR, int P>
 struct MinWaves {
     static constexpr int value = SCHEME == 1 ? (PREC == 2 ? 3 : 4)
