@@ -718,6 +718,16 @@ lm_status resolve_precision(lm_map* m, hipStream_t s)
     if (!st2 && own.ensure(kHistOff) != hipSuccess)
         return fail(LM_ENOMEM, "cannot allocate the precision probe");
     unsigned char* dev = st2 ? st2->scratch.as<unsigned char>() : own.as<unsigned char>();
+    // no kernel may write the set's scratch once it is given back: a launch that fails
+    // leaves those before it on the caller's stream
+    struct Drain {
+        hipStream_t s;
+        bool done = false;
+        ~Drain()
+        {
+            if (!done) (void)hipStreamSynchronize(s);
+        }
+    } drain{s};
     int64_t *di = reinterpret_cast<int64_t*>(dev), *dj = di + n;
     double* uv[3];  // plain, centred and FP64 near sums
     for (int k = 0; k < 3; ++k) uv[k] = reinterpret_cast<double*>(dev) + 2 * n * (k + 1);
@@ -732,6 +742,7 @@ lm_status resolve_precision(lm_map* m, hipStream_t s)
     double hp[3 * kParts];
     HIP_TRY(hipMemcpyAsync(hp, part, sizeof hp, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    drain.done = true;
     double acc = 0.0, acc_c = 0.0, n_in = 0.0;
     for (int k = 0; k < kParts; ++k) {
         acc += hp[3 * k];
